@@ -153,10 +153,11 @@ epl_status epl_dispatch(const epl_config *cfg, const void *x, const epl_layout_b
  * (Kernel Decomposition: the rows are placed as the tokens are sent). For bf16 payloads with at
  * most 256 pairs per layout chunk and at most 256 experts, the layout's finalize step (stable
  * rows, dedup slots) runs inside the dispatch kernel, which saves a launch; other configs run the
- * layout and then the dispatch (see epl_layout_dispatch_launches). Arguments are those of the two
+ * layout and then the dispatch. Small ones (T*k <= 16384 and Tr*k <= 4096) take a single launch whose
+ * workgroups work out their own tokens' rows and send them. Arguments are those of the two
  * calls, with the same meaning, alignment and capacity rules; every status those calls can
- * return is returned before any launch. It is exactly epl_layout_counts followed by
- * epl_dispatch_rows with the same arguments.                                                 */
+ * return is returned before any launch. Its outputs are those of epl_layout_counts followed by
+ * epl_dispatch_rows with the same arguments; the workspace's contents afterwards are unspecified. */
 epl_status epl_layout_dispatch(const epl_config *cfg, const int32_t *topk_idx, const epl_layout_buffers *L,
                                void *workspace, size_t workspace_bytes, const void *x, void *recv, float *recv_scale,
                                int64_t recv_rows_cap, void *stream);
@@ -389,14 +390,15 @@ epl_status epl_debug_f32_to_e4m3(const float *in, uint8_t *out, int64_t n, void 
 epl_status epl_debug_f32_to_bf16(const float *in, uint16_t *out, int64_t n, void *stream);
 
 /* Number of kernel launches epl_layout issues for cfg: 1 (each workgroup recomputes the global
- * counts it needs; used while T*k <= 16384, Tr*k <= 4096 and its LDS fits in 64 KiB) or 3
+ * counts it needs; used while T*k <= 16384, Tr*k <= 4096 and 9*E + 6*R <= 12287) or 3
  * (histogram, scan, finalize). Returns -1 if cfg is invalid. Host-only, no HIP calls.        */
 int epl_layout_launches(const epl_config *cfg);
 
-/* Kernel launches epl_layout_dispatch issues for cfg: 2 (one-launch layout, dispatch),
+/* Kernel launches of epl_layout_dispatch's two phases for cfg: 2 (one-launch layout, dispatch),
  * 3 (histogram, scan, finalize fused into the dispatch) or 4 (three-launch layout, dispatch).
- * epl_layout_counts issues all but the last of them. Returns -1 if cfg is invalid. Host-only,
- * no HIP calls.                                                                               */
+ * epl_layout_counts issues all but the last of them. epl_layout_dispatch issues the same ones, or a
+ * single launch where T*k <= 16384 and Tr*k <= 4096. Returns -1 if cfg is invalid. Host-only, no HIP
+ * calls.                                                                                      */
 int epl_layout_dispatch_launches(const epl_config *cfg);
 
 /* Static strings; never NULL. */

@@ -142,6 +142,18 @@ hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const int32_t* to
   return epl::launch_dispatch_bf16(x, L->pair_row, recv, g.T, cfg->topk, cfg->hidden, pitch_of(cfg), cap, s);
 }
 
+// Layout and dispatch: one launch for the geometries small_layout accepts, else the two phases.
+hipError_t run_layout_dispatch(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx,
+                               const epl_layout_buffers* L, int32_t* ws, const void* x, void* recv, float* recv_scale,
+                               int64_t cap, hipStream_t s) {
+  if (epl::small_layout(g))
+    return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap,
+                                             cfg->payload == EPL_PAYLOAD_FP8_E4M3, s);
+  const hipError_t e = run_counts(g, cfg, topk_idx, L, ws, s);
+  if (e != hipSuccess) return e;
+  return run_rows(g, cfg, topk_idx, L, ws, x, recv, recv_scale, cap, s);
+}
+
 }  // namespace
 
 EPL_EXPORT epl_status epl_layout(const epl_config* cfg, const int32_t* topk_idx, const epl_layout_buffers* L,
@@ -198,12 +210,8 @@ EPL_EXPORT epl_status epl_layout_dispatch(const epl_config* cfg, const int32_t* 
   const epl_status st =
       check_layout_dispatch(cfg, topk_idx, L, workspace, ws_bytes, x, recv, recv_scale, recv_rows_cap);
   if (st != EPL_OK) return st;
-  const epl::Geom g = make_geom(cfg);
-  const hipStream_t s = static_cast<hipStream_t>(stream);
-  int32_t* ws = static_cast<int32_t*>(workspace);
-  const hipError_t e = run_counts(g, cfg, topk_idx, L, ws, s);
-  if (e != hipSuccess) return from_hip(e);
-  return from_hip(run_rows(g, cfg, topk_idx, L, ws, x, recv, recv_scale, recv_rows_cap, s));
+  return from_hip(run_layout_dispatch(make_geom(cfg), cfg, topk_idx, L, static_cast<int32_t*>(workspace), x, recv,
+                                      recv_scale, recv_rows_cap, static_cast<hipStream_t>(stream)));
 }
 
 // ------------------------------------------------------------------ decomposed single launch
@@ -384,11 +392,9 @@ EPL_EXPORT epl_status epl_layout_dispatch_noalloc(const epl_config* cfg, const i
   if (st != EPL_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
   int32_t* ws = nullptr;
-  hipError_t e = device_scratch(s, &ws);
+  const hipError_t e = device_scratch(s, &ws);
   if (e != hipSuccess) return from_hip(e);
-  e = run_counts(g, cfg, topk_idx, L, ws, s);
-  if (e != hipSuccess) return from_hip(e);
-  return from_hip(run_rows(g, cfg, topk_idx, L, ws, x, recv, recv_scale, recv_rows_cap, s));
+  return from_hip(run_layout_dispatch(g, cfg, topk_idx, L, ws, x, recv, recv_scale, recv_rows_cap, s));
 }
 
 EPL_EXPORT int epl_layout_dispatch_launches(const epl_config* cfg) {

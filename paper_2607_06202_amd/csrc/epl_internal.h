@@ -19,13 +19,18 @@ constexpr int kLayoutWaves = kLayoutThreads / kWave;
 constexpr int kMaxChunkPairs = 1024;
 constexpr int kChunkSlots = kMaxChunkPairs / kLayoutThreads;  // register slots per lane
 constexpr int kLayoutSlots = EPL_MAX_EXPERTS / kLayoutThreads;  // per-lane slots covering E or R experts/ranks
-// The single-launch layout reads all T*k ids in every workgroup and walks each source rank's
-// earlier tokens again, so it is used only up to these sizes; larger layouts take three launches.
-// Measured on MI355X, the one-launch layout costs about 11 us + 12 us per 64K pairs, against
-// 17-22 us for three launches: it wins up to about 37K pairs.
+// The one-launch layout (small.hip) counts all T*k ids in every workgroup and deduplicates each source
+// rank's earlier tokens again, so it is used only up to these sizes; larger layouts take three
+// launches. Whole layer of 2048 columns, layout and dispatch in one launch against three: 16K pairs
+// on 32 ranks 35.9 / 39.2 us, 24K 56.2 / 55.2, 32K 71.6 / 69.2. The rank limit keeps the second pass
+// short: 16K pairs on one rank took 39.7 / 37.5 us, 16K of top-1 67.6 / 44.2, 12K on two ranks
+// 29.2 / 32.1.
 constexpr int64_t kSingleMaxPairs = 16384;     // T*k
 constexpr int64_t kSingleMaxRankPairs = 4096;  // Tr*k
-constexpr size_t kSingleMaxLds = 64 * 1024;    // bytes of LDS per workgroup
+// Bound on 9 E + 6 R for epl_layout alone, whose launch count (epl_layout_launches) it is part of.
+// epl_layout_dispatch has no such bound: 4K pairs on 1024 ranks of one expert take 26.6 us per layer in
+// one launch, 51.9 in three.
+constexpr int64_t kSingleMaxTable = 12287;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -250,8 +255,8 @@ __device__ __forceinline__ void st32(T* p, T v) {
 }
 
 // ---------------------------------------------------------------- launchers (host side)
-size_t single_lds_bytes(const Geom& g);
-bool layout_single(const Geom& g);  // true if epl_layout runs as one launch for this geometry
+bool small_layout(const Geom& g);   // true if epl_layout_dispatch runs as one launch for this geometry
+bool layout_single(const Geom& g);  // true if epl_layout does
 // K1 and K2 only: histograms, dedup masks and the prefix scans, left in the workspace for a
 // finalize step (route_finalize_kernel, or the fused finalize in the dispatch kernels).
 hipError_t launch_layout_counts(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* send_cnt, int32_t* rank_cnt,
@@ -264,6 +269,13 @@ hipError_t launch_layout(const Geom& g, const int32_t* idx, int32_t* ws, int32_t
                          int32_t* expert_off, int32_t* rank_off, int32_t* seg_off, int32_t* tok_nranks,
                          int32_t* pair_row, int32_t* pair_rslot, int32_t* recv_src, int32_t* recv_j,
                          int32_t* num_invalid, hipStream_t stream);
+
+// The geometries small_layout accepts: the layout in one launch, or layout and dispatch in one launch
+// (recv_scale for fp8 only).
+hipError_t launch_small_layout(const Geom& g, const int32_t* idx, const epl_layout_buffers& L, hipStream_t stream);
+hipError_t launch_small_layout_dispatch(const Geom& g, const int32_t* idx, const epl_layout_buffers& L, const void* x,
+                                        void* recv, float* recv_scale, int H, int pitch, int64_t cap, bool fp8,
+                                        hipStream_t stream);
 
 // pitch: elements from one recv row to the next (>= H, a multiple of 64).
 hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* recv, int64_t T, int k, int H,

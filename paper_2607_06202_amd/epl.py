@@ -848,8 +848,9 @@ def layout_launches(cfg: Config) -> int:
 
 
 def layout_dispatch_launches(cfg: Config) -> int:
-    """Kernel launches epl_layout_dispatch issues for cfg: 2, 3 (finalize fused into dispatch) or 4;
-    layout_counts issues all but the last."""
+    """Kernel launches of layout_dispatch's two phases for cfg: 2, 3 (finalize fused into dispatch) or 4;
+    layout_counts issues all but the last. layout_dispatch itself takes a single launch where
+    T*k <= 16384 and Tr*k <= 4096."""
     n = lib().epl_layout_dispatch_launches(ctypes.byref(cfg))
     if n < 0:
         raise EplError(1, "epl_layout_dispatch_launches")
