@@ -18,18 +18,28 @@
 
 namespace epl {
 
-// Waves per SIMD of the plain bf16 kernel. The instance that reads a large x through buffer loads
-// is held at exactly 6; the other is left unconstrained (1 to 8, which compiles to the same code
-// as no attribute; its register use allows 8). Layout -> dispatch -> combine with the input
-// rotated, dispatch per call, two runs each, caps 3 / 4 / 6 / unconstrained:
-// * EP=32 prefill (buffer loads): 3278-3281 / 3242 / 3238-3242 / 3279-3280 us;
-// * EP=256 (buffer loads): 385.9-386.5 / 382.2-382.5 / 375.9-376.7 / 380.8-381.0 us;
-// * EP=64 decode (plain loads): 180.9-181.1 / 181.5 / 179.7-179.8 / 176.2-176.6 us.
-constexpr int bf16_min_waves(bool buf_x) { return buf_x ? 6 : 1; }
-constexpr int bf16_max_waves(bool buf_x) { return buf_x ? 6 : 8; }
-template <bool BUF_X>
+// The plain bf16 kernel: one (token, 1 KiB column chunk) per wave, two waves per workgroup, held at 4
+// waves per SIMD. What bounds it is how scattered writes spread over the memory: in a write-only probe
+// 14 KiB rows in random order take 5.3 TB/s in 4 KiB pieces and 5.56 in 1 KiB pieces (in sequential
+// order 7.3). Small pieces of a row written from several XCDs (consecutive workgroups run on different
+// ones) measured best, and few at a time. Whole layer, expert outputs in a buffer of their own, us for
+// (piece, waves per workgroup, waves per SIMD):
+// * EP=64 decode: 4 KiB, 4, any 397; 1 KiB, 4, any 396; 1 KiB, 4, 3 381; 1 KiB, 2, 3 / 4 / 5 / 6
+//   379.4 / 378.8 / 381.4 / 390; 1 KiB, 7, 3 388; 1 KiB, 1, 4 379.4; 2 KiB, 2, 3 388; 4 KiB, 4, 3 399;
+// * EP=256: 4 KiB, 4, 6 769; 1 KiB, 4, any 777; 1 KiB, 2, 2 / 3 / 4 / 5 785 / 743.4 / 742.6 / 750;
+//   2 KiB, 2, 3 762; 4 KiB, 4, 3 785; neighbouring pieces on one XCD 773;
+// * EP=32 prefill: 4 KiB, 4, 6 6112; 1 KiB, 2, 3 / 4 / 5 5873 / 5877 / 6041.
+// Pieces of 512 or 256 bytes (several tokens per wave) were no faster (380-395 at decode). Loads of x
+// with the nt policy cost 6 us at decode; buffer loads change nothing.
+// With one or two choices a wave has little to write and more of them are needed: 6 waves per SIMD.
+// Whole layer, 4 KiB pieces / 1 KiB at 4 / at 6 waves: top-1 of 32K rows of 7168 columns 456 / 459 / 433,
+// of 64K rows of 1024 138.7 / 143.3 / 136.3; top-2 of 32K rows of 7168 606 / 575 / 585, of 32K rows of
+// 512 55.1 / 57.2 / 55.5; top-4 of 16K rows of 4096 259 / 243 / 248.
+constexpr int plain_waves_per_simd(bool few) { return few ? 6 : 4; }
+constexpr int kFewChoices = 2;
+template <bool FEW>
 __global__ void __launch_bounds__(kPlainThreads)
-    __attribute__((amdgpu_waves_per_eu(bf16_min_waves(BUF_X), bf16_max_waves(BUF_X))))
+    __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd(FEW), plain_waves_per_simd(FEW))))
     dispatch_bf16_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row, u32x4* __restrict__ recv,
                          int64_t T, int k, int nv, int pv, int chunks, int64_t cap) {
   const int lane = threadIdx.x % kWave;
@@ -37,7 +47,7 @@ __global__ void __launch_bounds__(kPlainThreads)
   const int64_t stride = (int64_t)gridDim.x * kPlainWaves;
   for (int64_t u = (int64_t)blockIdx.x * kPlainWaves + threadIdx.x / kWave; u < units; u += stride) {
     const int64_t g = u / chunks;
-    dispatch_bf16_unit<BUF_X>(
+    dispatch_bf16_unit<false, 1>(
         x, [&] { return lane < k ? pair_row[g * k + lane] : -1; }, recv, g, (int)(u - g * chunks), k, nv, pv, cap,
         lane);
   }
@@ -73,17 +83,17 @@ hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* re
                                 int pitch, int64_t cap, hipStream_t stream) {
   if (T == 0) return hipSuccess;
   const int nv = H / 8;
-  const int chunks = (nv + kBf16Cols - 1) / kBf16Cols;
+  const int chunks = (nv + kWave - 1) / kWave;
   const int64_t units = T * chunks;
   const dim3 grid((unsigned)std::min<int64_t>((units + kPlainWaves - 1) / kPlainWaves, 1 << 30));
-  if (T * (int64_t)H * 2 >= kBufferLoadXBytes)
-    hipLaunchKernelGGL(dispatch_bf16_kernel<true>, grid, dim3(kPlainThreads), 0, stream,
-                       static_cast<const u32x4*>(x), pair_row, static_cast<u32x4*>(recv), T, k, nv, pitch / 8, chunks,
-                       cap);
+  const u32x4* xv = static_cast<const u32x4*>(x);
+  u32x4* rv = static_cast<u32x4*>(recv);
+  if (k <= kFewChoices)
+    hipLaunchKernelGGL(dispatch_bf16_kernel<true>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, T, k, nv,
+                       pitch / 8, chunks, cap);
   else
-    hipLaunchKernelGGL(dispatch_bf16_kernel<false>, grid, dim3(kPlainThreads), 0, stream,
-                       static_cast<const u32x4*>(x), pair_row, static_cast<u32x4*>(recv), T, k, nv, pitch / 8, chunks,
-                       cap);
+    hipLaunchKernelGGL(dispatch_bf16_kernel<false>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, T, k, nv,
+                       pitch / 8, chunks, cap);
   return hipGetLastError();
 }
 

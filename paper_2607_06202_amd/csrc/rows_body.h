@@ -10,15 +10,14 @@ namespace epl {
 
 constexpr int kDispatchThreads = 256;  // the fused kernel (its metadata workgroups scan with layout-sized blocks)
 constexpr int kWavesPerBlock = kDispatchThreads / kWave;
-// Workgroup sizes of the plain kernels. Whole layer, two runs each, dispatch us with 128 / 256 /
-// 512 threads: decode (bf16) 183.4-183.6 / 177.7-178.0 / 178.6-179.2; EP=256 (bf16) 396.8-397.1 /
-// 375.8-376.2 / 389.0-389.3; prefill (bf16) 3327 / 3239-3243 / 3282-3284; skewed fp8 202.3-203.2 /
-// 205.3-205.4 / 228.6.
-constexpr int kPlainThreads = 256;     // the plain bf16 dispatch kernel
+// Workgroup sizes of the plain kernels. The bf16 kernel's is measured beside it; fp8, whole layer, two
+// runs each, dispatch us with 128 / 256 / 512 threads: skewed fp8 202.3-203.2 / 205.3-205.4 / 228.6.
+constexpr int kPlainThreads = 128;     // the plain bf16 dispatch kernel
 constexpr int kPlainWaves = kPlainThreads / kWave;
 constexpr int kFp8Threads = 128;       // the fp8 dispatch kernel
 constexpr int kFp8Waves = kFp8Threads / kWave;
-// bf16 work unit: one token's columns [u*kBf16Cols, (u+1)*kBf16Cols) in 16-byte vectors.
+// bf16 work unit of the kernels that place rows as they send them: one token's columns
+// [u*kBf16Cols, (u+1)*kBf16Cols) in 16-byte vectors. The plain kernel's units are one vector per lane.
 constexpr int kBf16VPL = 4;                     // vectors per lane in one unit
 constexpr int kBf16Cols = kWave * kBf16VPL;     // 256 vectors = 4 KiB of a row
 constexpr int64_t kBufferLoadXBytes = 200ll << 20;  // x at least this large: buffer loads (see dispatch_bf16_unit)
@@ -37,7 +36,7 @@ __device__ __forceinline__ void store_row_policy(u32x4 val, u32x4* row_base, int
   __builtin_amdgcn_raw_buffer_store_b128(val, rsrc, v * 16, 0, POLICY);
 }
 
-// bf16: unit = (token g, column chunk c). The wave loads its chunk of x[g] once and stores it
+// bf16: unit = (token g, column chunk c of VPL vectors per lane). The wave loads its chunk of x[g] once and stores it
 // to the k destination rows, interleaving destinations per vector. x rows are nv vectors apart,
 // recv rows pv (the receive pitch in 16-byte vectors).
 //
@@ -60,33 +59,33 @@ struct NoCheck {
 struct NoAfter {
   __device__ __forceinline__ void operator()(const u32x4*, const bool*, int) const {}
 };
-template <bool BUF_X, class RowFn, class CheckFn = NoCheck, class AfterFn = NoAfter>
+template <bool BUF_X, int VPL = kBf16VPL, class RowFn, class CheckFn = NoCheck, class AfterFn = NoAfter>
 __device__ __forceinline__ void dispatch_bf16_unit(const u32x4* __restrict__ x, RowFn row_of, u32x4* __restrict__ recv,
                                                    int64_t g, int c, int k, int nv, int pv, int64_t cap, int lane,
                                                    bool active = true, CheckFn check = CheckFn(),
                                                    AfterFn after = AfterFn()) {
   const u32x4* xr = x + g * nv;
-  const int v0 = c * kBf16Cols + lane;
+  const int v0 = c * (kWave * VPL) + lane;
   // Loads are unconditional (index clamped into the row) so that all of them are in flight
   // together; only the stores are guarded. Default cache policy: it measured faster than
   // nontemporal loads here, though x is read once.
-  u32x4 buf[kBf16VPL];
+  u32x4 buf[VPL];
   if constexpr (BUF_X) {
     const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(xr), 0, nv * 16, kBufferRsrcWord3);
 #pragma unroll
-    for (int u = 0; u < kBf16VPL; ++u) buf[u] = __builtin_amdgcn_raw_buffer_load_b128(xs, min(v0 + u * kWave, nv - 1) * 16, 0, 0);
+    for (int u = 0; u < VPL; ++u) buf[u] = __builtin_amdgcn_raw_buffer_load_b128(xs, min(v0 + u * kWave, nv - 1) * 16, 0, 0);
   } else {
 #pragma unroll
-    for (int u = 0; u < kBf16VPL; ++u) buf[u] = xr[min(v0 + u * kWave, nv - 1)];
+    for (int u = 0; u < VPL; ++u) buf[u] = xr[min(v0 + u * kWave, nv - 1)];
   }
   const int my_row = row_of();
   if (!active) return;
-  bool on[kBf16VPL];
+  bool on[VPL];
 #pragma unroll
-  for (int u = 0; u < kBf16VPL; ++u) on[u] = v0 + u * kWave < nv;
+  for (int u = 0; u < VPL; ++u) on[u] = v0 + u * kWave < nv;
   check(buf, on);
 #pragma unroll
-  for (int u = 0; u < kBf16VPL; ++u) {
+  for (int u = 0; u < VPL; ++u) {
     const int v = v0 + u * kWave;
     for (int j = 0; j < k; ++j) {
       const int row = __builtin_amdgcn_readlane(my_row, j);
