@@ -119,23 +119,20 @@ bool rows_fused(const epl::Geom& g, const epl_config* cfg) {
   return !epl::layout_single(g) && epl::fused_dispatch_ok(g, cfg->payload == EPL_PAYLOAD_FP8_E4M3);
 }
 
-// The layout kernels the row kernel does not take over: histogram and scan when the finalize
-// step is fused into the row kernel, otherwise the whole layout.
+// The layout: histogram and place for the fused geometries, whose row kernel writes recv_src and recv_j,
+// otherwise all of it.
 hipError_t run_counts(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx,
                       const epl_layout_buffers* L, int32_t* ws, hipStream_t s) {
-  if (rows_fused(g, cfg))
-    return epl::launch_layout_counts(g, topk_idx, ws, L->send_cnt, L->rank_cnt, L->tok_nranks, L->num_invalid, s);
+  if (rows_fused(g, cfg)) return epl::launch_layout_place(g, topk_idx, ws, *L, false, s);
   return epl::launch_layout(g, topk_idx, ws, L->send_cnt, L->rank_cnt, L->expert_off, L->rank_off, L->seg_off,
                             L->tok_nranks, L->pair_row, L->pair_rslot, L->recv_src, L->recv_j, L->num_invalid, s);
 }
 
-// One kernel: the fused finalize-and-send kernel, or the plain bf16 / fp8 dispatch kernel.
-hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx, const epl_layout_buffers* L,
-                    int32_t* ws, const void* x, void* recv, float* recv_scale, int64_t cap, hipStream_t s) {
+// One kernel: the fused row kernel, or the plain bf16 / fp8 dispatch kernel.
+hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const epl_layout_buffers* L, const void* x, void* recv, float* recv_scale, int64_t cap, hipStream_t s) {
   if (rows_fused(g, cfg))
-    return epl::launch_fused_dispatch(g, topk_idx, ws, L->expert_off, L->rank_off, L->seg_off, L->pair_row,
-                                      L->pair_rslot, L->recv_src, L->recv_j, x, recv, cfg->hidden, pitch_of(cfg),
-                                      cap, s);
+    return epl::launch_fused_dispatch(x, L->pair_row, recv, L->recv_src, L->recv_j, g.T, cfg->topk, cfg->hidden,
+                                      pitch_of(cfg), cap, s);
   if (cfg->payload == EPL_PAYLOAD_FP8_E4M3)
     return epl::launch_dispatch_fp8(x, L->pair_row, recv, recv_scale, g.T, cfg->topk, cfg->hidden, pitch_of(cfg),
                                     cap, s);
@@ -149,9 +146,18 @@ hipError_t run_layout_dispatch(const epl::Geom& g, const epl_config* cfg, const 
   if (epl::small_layout(g))
     return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap,
                                              cfg->payload == EPL_PAYLOAD_FP8_E4M3, s);
-  const hipError_t e = run_counts(g, cfg, topk_idx, L, ws, s);
-  if (e != hipSuccess) return e;
-  return run_rows(g, cfg, topk_idx, L, ws, x, recv, recv_scale, cap, s);
+  const bool fp8 = cfg->payload == EPL_PAYLOAD_FP8_E4M3;
+  hipError_t e;
+  if (!epl::place_layout(g)) {
+    if ((e = run_counts(g, cfg, topk_idx, L, ws, s)) != hipSuccess) return e;
+    return run_rows(g, cfg, L, x, recv, recv_scale, cap, s);
+  }
+  if ((e = epl::launch_layout_place(g, topk_idx, ws, *L, fp8, s)) != hipSuccess) return e;
+  if (fp8)
+    return epl::launch_dispatch_fp8(x, L->pair_row, recv, recv_scale, g.T, cfg->topk, cfg->hidden, pitch_of(cfg),
+                                    cap, s);
+  return epl::launch_fused_dispatch(x, L->pair_row, recv, L->recv_src, L->recv_j, g.T, cfg->topk, cfg->hidden,
+                                    pitch_of(cfg), cap, s);
 }
 
 }  // namespace
@@ -200,8 +206,7 @@ EPL_EXPORT epl_status epl_dispatch_rows(const epl_config* cfg, const int32_t* to
   const epl_status st =
       check_layout_dispatch(cfg, topk_idx, L, workspace, ws_bytes, x, recv, recv_scale, recv_rows_cap);
   if (st != EPL_OK) return st;
-  return from_hip(run_rows(make_geom(cfg), cfg, topk_idx, L, static_cast<int32_t*>(workspace), x, recv, recv_scale,
-                           recv_rows_cap, static_cast<hipStream_t>(stream)));
+  return from_hip(run_rows(make_geom(cfg), cfg, L, x, recv, recv_scale, recv_rows_cap, static_cast<hipStream_t>(stream)));
 }
 
 EPL_EXPORT epl_status epl_layout_dispatch(const epl_config* cfg, const int32_t* topk_idx, const epl_layout_buffers* L,

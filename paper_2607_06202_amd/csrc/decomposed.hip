@@ -479,7 +479,7 @@ void launch_variant(int sync, dim3 grid, dim3 block, size_t lds, hipStream_t str
 }
 
 size_t decomposed_lds_bytes(const Geom& g) {
-  const size_t hist = (size_t)g.E + g.R + kMaxChunkPairs;                       // K1
+  const size_t hist = (size_t)g.E + g.R;                                        // K1
   const size_t rows = (size_t)kWavesPerBlock * (EPL_MAX_TOPK + g.E + g.R);      // row placement
   const size_t meta = (size_t)g.E + 1;                                           // offsets
   return sizeof(int32_t) * std::max(hist, std::max(rows, meta));

@@ -37,20 +37,49 @@ namespace epl {
 // 512 55.1 / 57.2 / 55.5; top-4 of 16K rows of 4096 259 / 243 / 248.
 constexpr int plain_waves_per_simd(bool few) { return few ? 6 : 4; }
 constexpr int kFewChoices = 2;
-template <bool FEW>
-__global__ void __launch_bounds__(kPlainThreads)
-    __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd(FEW), plain_waves_per_simd(FEW))))
-    dispatch_bf16_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row, u32x4* __restrict__ recv,
-                         int64_t T, int k, int nv, int pv, int chunks, int64_t cap) {
+template <class AtFn>
+__device__ __forceinline__ void plain_units(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row,
+                                            u32x4* __restrict__ recv, int64_t T, int k, int nv, int pv, int chunks,
+                                            int64_t cap, AtFn at) {
   const int lane = threadIdx.x % kWave;
   const int64_t units = T * chunks;
   const int64_t stride = (int64_t)gridDim.x * kPlainWaves;
   for (int64_t u = (int64_t)blockIdx.x * kPlainWaves + threadIdx.x / kWave; u < units; u += stride) {
     const int64_t g = u / chunks;
+    const int c = (int)(u - g * chunks);
     dispatch_bf16_unit<false, 1>(
-        x, [&] { return lane < k ? pair_row[g * k + lane] : -1; }, recv, g, (int)(u - g * chunks), k, nv, pv, cap,
-        lane);
+        x,
+        [&] {
+          const int row = lane < k ? pair_row[g * k + lane] : -1;
+          at(g, c, lane, row);
+          return row;
+        },
+        recv, g, c, k, nv, pv, cap, lane);
   }
+}
+
+template <bool FEW>
+__global__ void __launch_bounds__(kPlainThreads)
+    __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd(FEW), plain_waves_per_simd(FEW))))
+    dispatch_bf16_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row, u32x4* __restrict__ recv,
+                         int64_t T, int k, int nv, int pv, int chunks, int64_t cap) {
+  plain_units(x, pair_row, recv, T, k, nv, pv, chunks, cap, [](int64_t, int, int, int) {});
+}
+
+// The same after the place kernel, which leaves recv_src and recv_j to the wave that sends a token's
+// first columns: 4-byte stores to scattered rows, hidden among the row stores.
+template <bool FEW>
+__global__ void __launch_bounds__(kPlainThreads)
+    __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd(FEW), plain_waves_per_simd(FEW))))
+    fused_bf16_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row, u32x4* __restrict__ recv,
+                      int32_t* __restrict__ recv_src, int32_t* __restrict__ recv_j, int64_t T, int k, int nv, int pv,
+                      int chunks, int64_t cap) {
+  plain_units(x, pair_row, recv, T, k, nv, pv, chunks, cap, [&](int64_t g, int c, int lane, int row) {
+    if (c == 0 && row >= 0 && row < T * k) {
+      recv_src[row] = (int32_t)g;
+      recv_j[row] = lane;
+    }
+  });
 }
 
 // The fp8 kernel is capped at kFp8WavesPerSimd waves per SIMD. The compiler enforces the cap by
@@ -97,6 +126,29 @@ hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* re
   return hipGetLastError();
 }
 
+hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* recv, int32_t* recv_src,
+                                 int32_t* recv_j, int64_t T, int k, int H, int pitch, int64_t cap,
+                                 hipStream_t stream) {
+  if (T == 0) return hipSuccess;
+  const int nv = H / 8;
+  const int chunks = (nv + kWave - 1) / kWave;
+  const int64_t units = T * chunks;
+  const dim3 grid((unsigned)std::min<int64_t>((units + kPlainWaves - 1) / kPlainWaves, 1 << 30));
+  const u32x4* xv = static_cast<const u32x4*>(x);
+  u32x4* rv = static_cast<u32x4*>(recv);
+  if (k <= kFewChoices)
+    hipLaunchKernelGGL(fused_bf16_kernel<true>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, recv_src,
+                       recv_j, T, k, nv, pitch / 8, chunks, cap);
+  else
+    hipLaunchKernelGGL(fused_bf16_kernel<false>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, recv_src,
+                       recv_j, T, k, nv, pitch / 8, chunks, cap);
+  return hipGetLastError();
+}
+
+bool fused_dispatch_ok(const Geom& g, bool fp8) {
+  return !fp8 && g.CT * g.k <= kFusedSlots * kWave && g.E <= kFusedPer * kWave;
+}
+
 hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* recv, float* recv_scale, int64_t T,
                                int k, int H, int pitch, int64_t cap, hipStream_t stream) {
   if (T == 0) return hipSuccess;
@@ -105,100 +157,6 @@ hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* rec
   const dim3 grid((unsigned)std::min<int64_t>((units + kFp8Waves - 1) / kFp8Waves, 1 << 30));
   hipLaunchKernelGGL(dispatch_fp8_kernel, grid, dim3(kFp8Threads), 0, stream, static_cast<const u32x4*>(x),
                      pair_row, static_cast<u32x4*>(recv), recv_scale, T, k, H, pitch / 16, npass, cap);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------ layout finalize fused into dispatch
-// epl_layout_dispatch runs K1 and K2 of the layout, then one kernel that does both the layout's
-// finalize step and the dispatch. No workgroup waits on another; the rows of each token are worked
-// out inside its workgroup from what K1 and K2 left in the workspace, with exactly the definitions
-// route_finalize_kernel applies to a whole chunk:
-// * row of pair (g, j) = first row of its expert (exclusive prefix of recv_cnt)
-//                      + rows of the expert before the token's chunk (K2's chunk offsets)
-//                      + earlier pairs of the chunk with the same expert (an LDS histogram of the
-//                        chunk's earlier tokens plus a ballot match over the token's own choices);
-// * slot of a first pair = slots of its rank before the chunk (K2) + earlier first pairs of the
-//   chunk bound for that rank; other valid pairs share the slot of their token's first pair on
-//   the same rank.
-// A workgroup's waves cover consecutive units, so they share few tokens (one when a row has as
-// many column chunks as the workgroup has waves). Wave w computes the rows of the workgroup's
-// w-th token, writes that token's pair_row, pair_rslot, recv_src and recv_j, and leaves the rows
-// in LDS for the other waves. A few extra workgroups at the start of the grid write expert_off,
-// rank_off and seg_off. The loads of x are issued before the row computation, so they are in
-// flight while it runs.
-template <bool BUF_X>
-__global__ void __launch_bounds__(kDispatchThreads)
-    fused_bf16_kernel(FusedLayout F, const u32x4* __restrict__ x, u32x4* __restrict__ recv, int nv, int pv,
-                      int chunks, int64_t cap, int unit_grid, int nmeta) {
-  extern __shared__ int32_t lds[];
-  // The metadata workgroups come first in the grid, so that they run alongside the units
-  // instead of after them.
-  if ((int)blockIdx.x < nmeta) {
-    fused_meta_block<false>(F, (int)blockIdx.x, nmeta, lds);
-    return;
-  }
-  const int blk = (int)blockIdx.x - nmeta;
-  const int lane = threadIdx.x % kWave;
-  const int w = threadIdx.x / kWave;
-  const int k = F.G.k;
-  int32_t* rows_lds = lds;  // [kWavesPerBlock][k]
-  int32_t* hist = lds + kWavesPerBlock * EPL_MAX_TOPK + w * (F.G.E + F.G.R);
-  const int64_t units = F.G.T * chunks;
-  const int64_t stride = (int64_t)unit_grid * kWavesPerBlock;
-  // The loop bound depends on the workgroup's first unit only, so every wave runs the same
-  // iterations and reaches the same barriers.
-  for (int64_t ub = (int64_t)blk * kWavesPerBlock; ub < units; ub += stride) {
-    const int64_t g_first = ub / chunks;
-    const int64_t g_last = std::min(units - 1, ub + kWavesPerBlock - 1) / chunks;
-    const int64_t u = ub + w;
-    const bool active = u < units;
-    const int64_t g = (active ? u : units - 1) / chunks;
-    const int c = (int)((active ? u : units - 1) - g * chunks);
-    dispatch_bf16_unit<BUF_X>(
-        x,
-        [&] {
-          if (w <= g_last - g_first) {
-            const int r = token_rows<false>(F, g_first + w, true, hist, lane);
-            if (lane < k) rows_lds[w * k + lane] = r;
-          }
-          __syncthreads();
-          const int r = lane < k ? rows_lds[(g - g_first) * k + lane] : -1;
-          __syncthreads();  // every wave has its rows before the next iteration rewrites them
-          return r;
-        },
-        recv, g, c, k, nv, pv, cap, lane, active);
-  }
-}
-
-bool fused_dispatch_ok(const Geom& g, bool fp8) {
-  return !fp8 && g.CT * g.k <= kFusedSlots * kWave && g.E <= kFusedPer * kWave;
-}
-
-hipError_t launch_fused_dispatch(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* expert_off,
-                                 int32_t* rank_off, int32_t* seg_off, int32_t* pair_row, int32_t* pair_rslot,
-                                 int32_t* recv_src, int32_t* recv_j, const void* x, void* recv, int H, int pitch,
-                                 int64_t cap, hipStream_t stream) {
-  const WsLayout wl = ws_layout(g);
-  const FusedLayout F{g,          idx,          ws + wl.chunk_e, ws + wl.chunk_r,
-                      ws + wl.recv_cnt, ws + wl.seg_rel, reinterpret_cast<const uint32_t*>(ws + wl.fmask),
-                      expert_off, rank_off,     seg_off,         pair_row,
-                      pair_rslot, recv_src,     recv_j};
-  const int nmeta = (int)std::max<int64_t>(1, ((int64_t)g.E * g.R + 4 * kDispatchThreads - 1) / (4 * kDispatchThreads));
-  const int chunks = (H / 8 + kBf16Cols - 1) / kBf16Cols;
-  const int64_t units = g.T * chunks;
-  const int unit_grid = (int)std::min<int64_t>((units + kWavesPerBlock - 1) / kWavesPerBlock, 1 << 30);
-  const dim3 grid((unsigned)(unit_grid + nmeta));
-  const size_t lds = sizeof(int32_t) * std::max<size_t>((size_t)kWavesPerBlock * (EPL_MAX_TOPK + g.E + g.R),
-                                                        (size_t)g.E + 1);
-  const bool buf_x = g.T * (int64_t)H * 2 >= kBufferLoadXBytes;
-  const u32x4* xv = static_cast<const u32x4*>(x);
-  u32x4* rv = static_cast<u32x4*>(recv);
-  if (buf_x)
-    hipLaunchKernelGGL(fused_bf16_kernel<true>, grid, dim3(kDispatchThreads), lds, stream, F, xv, rv, H / 8,
-                       pitch / 8, chunks, cap, unit_grid, nmeta);
-  else
-    hipLaunchKernelGGL(fused_bf16_kernel<false>, grid, dim3(kDispatchThreads), lds, stream, F, xv, rv, H / 8,
-                       pitch / 8, chunks, cap, unit_grid, nmeta);
   return hipGetLastError();
 }
 

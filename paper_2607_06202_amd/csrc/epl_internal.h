@@ -17,7 +17,6 @@ constexpr int kLayoutWaves = kLayoutThreads / kWave;
 // Pairs handled by one layout workgroup ("chunk"); a chunk never spans two source ranks and
 // always holds whole tokens.
 constexpr int kMaxChunkPairs = 1024;
-constexpr int kChunkSlots = kMaxChunkPairs / kLayoutThreads;  // register slots per lane
 constexpr int kLayoutSlots = EPL_MAX_EXPERTS / kLayoutThreads;  // per-lane slots covering E or R experts/ranks
 // The one-launch layout (small.hip) counts all T*k ids in every workgroup and deduplicates each source
 // rank's earlier tokens again, so it is used only up to these sizes; larger layouts take three
@@ -54,13 +53,15 @@ struct Geom {
 
 // Workspace carve-up, in int32 elements.
 struct WsLayout {
-  size_t chunk_e;   // [E][nblk]  per-chunk expert counts, then chunk base rows within the expert
+  size_t chunk_e;   // [E][nblk]  per-chunk expert counts, then chunk base rows within the expert (for the
+                    //            place kernel [nblk/4][(E+1)/2] pairs of 16-bit counts of four chunks)
   size_t chunk_r;   // [nblk][R]  per-chunk first-pair counts per destination rank, then slot bases
   size_t recv_cnt;  // [E]
   size_t inval;     // [nblk]
   size_t seg_rel;   // [E][R]     segment offsets relative to the expert start
-  size_t fmask;     // [T]        per-token bitmask of first pairs per destination rank
-  size_t cnt;       // [nblk][E]  per-chunk expert counts, chunk-major (the decomposed layer's K1 rows)
+  size_t fmask;     // [T]        per-token bitmask of first pairs per destination rank (the decomposed launch)
+  size_t cnt;       // [nblk][E]  per-chunk expert counts, chunk-major (the decomposed launch's K1 rows; for the
+                    //            place kernel [nblk][(E+1)/2] pairs of 16-bit counts)
   size_t sync;      // [kSyncWords] completion words of the decomposed layer, 256-byte aligned
   size_t total;
 };
@@ -257,14 +258,19 @@ __device__ __forceinline__ void st32(T* p, T v) {
 // ---------------------------------------------------------------- launchers (host side)
 bool small_layout(const Geom& g);   // true if epl_layout_dispatch runs as one launch for this geometry
 bool layout_single(const Geom& g);  // true if epl_layout does
-// K1 and K2 only: histograms, dedup masks and the prefix scans, left in the workspace for a
-// finalize step (route_finalize_kernel, or the fused finalize in the dispatch kernels).
+// K1 and K2 only: histograms and the prefix scans, left in the workspace for route_finalize_kernel.
 hipError_t launch_layout_counts(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* send_cnt, int32_t* rank_cnt,
                                 int32_t* tok_nranks, int32_t* num_invalid, hipStream_t stream);
 // K3 only, after launch_layout_counts on the same stream.
 hipError_t launch_layout_finalize(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* expert_off,
                                   int32_t* rank_off, int32_t* seg_off, int32_t* pair_row, int32_t* pair_rslot,
                                   int32_t* recv_src, int32_t* recv_j, hipStream_t stream);
+// Layouts whose [nblk][E] count matrix every workgroup can sum for itself: the whole layout in two launches
+// (count and place), recv_src and recv_j only with write_src.
+constexpr int kPlaceMaxChunks = 512;
+bool place_layout(const Geom& g);
+hipError_t launch_layout_place(const Geom& g, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
+                               bool write_src, hipStream_t stream);
 hipError_t launch_layout(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* send_cnt, int32_t* rank_cnt,
                          int32_t* expert_off, int32_t* rank_off, int32_t* seg_off, int32_t* tok_nranks,
                          int32_t* pair_row, int32_t* pair_rslot, int32_t* recv_src, int32_t* recv_j,
@@ -282,13 +288,13 @@ hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* re
                                 int pitch, int64_t cap, hipStream_t stream);
 hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* recv, float* recv_scale, int64_t T,
                                int k, int H, int pitch, int64_t cap, hipStream_t stream);
-// The layout's finalize step fused into the bf16 dispatch (after launch_layout_counts on the same
-// stream), for the geometries fused_dispatch_ok accepts.
+// The bf16 dispatch after launch_layout_place without write_src: it also writes recv_src and recv_j.
+hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* recv, int32_t* recv_src,
+                                 int32_t* recv_j, int64_t T, int k, int H, int pitch, int64_t cap,
+                                 hipStream_t stream);
+// The geometries whose two phases are launch_layout_place and launch_fused_dispatch, and which the
+// decomposed launch takes.
 bool fused_dispatch_ok(const Geom& g, bool fp8);
-hipError_t launch_fused_dispatch(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* expert_off,
-                                 int32_t* rank_off, int32_t* seg_off, int32_t* pair_row, int32_t* pair_rslot,
-                                 int32_t* recv_src, int32_t* recv_j, const void* x, void* recv, int H, int pitch,
-                                 int64_t cap, hipStream_t stream);
 // The decomposed single-launch layout and dispatch (bf16, the geometries fused_dispatch_ok
 // accepts). count_groups 0 picks the default split; spin_ticks bounds every wait (100 MHz ticks);
 // ready_target is the published value the send workgroups wait for (1; a test passes 2 to force a

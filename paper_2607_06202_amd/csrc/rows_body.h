@@ -1,14 +1,14 @@
-// Device bodies of the row kernels that place each token's pairs as they send them, shared by
-// the fused finalize-and-send kernel (dispatch.hip) and the decomposed single-launch layer
-// (decomposed.hip), where they read the layout data other workgroups of the same kernel wrote
-// with device-scope loads (the C template argument, see ld32).
+// Device bodies of the row kernels: the units the dispatch kernels send (dispatch.hip, small.hip,
+// schedule.hip), and the placement of a token's pairs from the decomposed single launch's counts
+// (decomposed.hip), which reads the layout data other workgroups of the same kernel wrote with
+// device-scope loads (the C template argument, see ld32).
 #pragma once
 
 #include "epl_internal.h"
 
 namespace epl {
 
-constexpr int kDispatchThreads = 256;  // the fused kernel (its metadata workgroups scan with layout-sized blocks)
+constexpr int kDispatchThreads = 256;  // the decomposed launch (its metadata workgroups scan with layout-sized blocks)
 constexpr int kWavesPerBlock = kDispatchThreads / kWave;
 // Workgroup sizes of the plain kernels. The bf16 kernel's is measured beside it; fp8, whole layer, two
 // runs each, dispatch us with 128 / 256 / 512 threads: skewed fp8 202.3-203.2 / 205.3-205.4 / 228.6.
@@ -16,7 +16,7 @@ constexpr int kPlainThreads = 128;     // the plain bf16 dispatch kernel
 constexpr int kPlainWaves = kPlainThreads / kWave;
 constexpr int kFp8Threads = 128;       // the fp8 dispatch kernel
 constexpr int kFp8Waves = kFp8Threads / kWave;
-// bf16 work unit of the kernels that place rows as they send them: one token's columns
+// bf16 work unit of the one-launch and scheduled kernels: one token's columns
 // [u*kBf16Cols, (u+1)*kBf16Cols) in 16-byte vectors. The plain kernel's units are one vector per lane.
 constexpr int kBf16VPL = 4;                     // vectors per lane in one unit
 constexpr int kBf16Cols = kWave * kBf16VPL;     // 256 vectors = 4 KiB of a row
@@ -41,13 +41,10 @@ __device__ __forceinline__ void store_row_policy(u32x4 val, u32x4* row_base, int
 // recv rows pv (the receive pitch in 16-byte vectors).
 //
 // BUF_X selects how x is read, both with the default cache policy: buffer loads through a
-// resource bounded to the row, or plain global loads. Measured over three repetitions each
-// (dispatch alone, x rotated):
-// * EP=32 prefill: 3293 -> 3252 us with buffer loads;
-// * EP=256: 380.5 -> 376.3 us with buffer loads;
-// * EP=64 decode: 176.4 -> 178.1 us, slower with buffer loads.
-// The launcher takes buffer loads for an x of 200 MB or more, a threshold between decode's 117 MB
-// and the 235 MB and 1.9 GB of the others; why the instruction form matters is not established.
+// resource bounded to the row, or plain global loads. With 4 KiB units, dispatch alone, x rotated, global
+// against buffer loads: EP=32 prefill 3293 / 3252 us, EP=256 380.5 / 376.3, EP=64 decode 176.4 / 178.1. The
+// decomposed and scheduled launches take buffer loads for an x of 200 MB or more, between decode's
+// 117 MB and the others' 235 MB and 1.9 GB; with 1 KiB units the form makes no difference.
 // row_of() returns, in lane j < k, the packed row of pair j (-1 if invalid); it is called after the
 // loads of x are issued, so whatever it loads is in flight together with them. An inactive wave
 // loads and calls row_of() (which may hold a workgroup barrier) but stores nothing. check(buf, on)
@@ -162,7 +159,7 @@ struct FusedLayout {
   int32_t* recv_j;
 };
 
-// Sizes the fused kernel is built for: at most kFusedSlots * 64 pairs per chunk (CT * k) and
+// Sizes token_rows is built for: at most kFusedSlots * 64 pairs per chunk (CT * k) and
 // kFusedPer * 64 experts. hist is this wave's LDS [E + R].
 constexpr int kFusedSlots = 4;
 constexpr int kFusedPer = 4;

@@ -308,8 +308,8 @@ def layout(cfg: Config, topk_idx: torch.Tensor, out: Layout | None = None) -> La
 
 
 def layout_counts(cfg: Config, topk_idx: torch.Tensor, out: Layout | None = None) -> Layout:
-    """epl_layout_counts: first phase of layout_dispatch (the layout kernels the row kernel does
-    not take over) -> Layout, complete only after dispatch_rows."""
+    """epl_layout_counts: first phase of layout_dispatch (the layout kernels) -> Layout, complete only
+    after dispatch_rows."""
     dev = topk_idx.device
     L = _layout_args(cfg, topk_idx, out)
     bufs = L.buffers()
@@ -848,9 +848,9 @@ def layout_launches(cfg: Config) -> int:
 
 
 def layout_dispatch_launches(cfg: Config) -> int:
-    """Kernel launches of layout_dispatch's two phases for cfg: 2, 3 (finalize fused into dispatch) or 4;
-    layout_counts issues all but the last. layout_dispatch itself takes a single launch where
-    T*k <= 16384 and Tr*k <= 4096."""
+    """Kernel launches of layout_dispatch's two phases for cfg: 2, 3 or 4; layout_counts issues all but the
+    last. layout_dispatch itself issues no more than these: a single one where T*k <= 16384 and
+    Tr*k <= 4096, three for layouts of at most 512 chunks and 256 experts."""
     n = lib().epl_layout_dispatch_launches(ctypes.byref(cfg))
     if n < 0:
         raise EplError(1, "epl_layout_dispatch_launches")
