@@ -43,8 +43,8 @@ __device__ __forceinline__ void store_row_policy(u32x4 val, u32x4* row_base, int
 // BUF_X selects how x is read, both with the default cache policy: buffer loads through a
 // resource bounded to the row, or plain global loads. With 4 KiB units, dispatch alone, x rotated, global
 // against buffer loads: EP=32 prefill 3293 / 3252 us, EP=256 380.5 / 376.3, EP=64 decode 176.4 / 178.1. The
-// decomposed and scheduled launches take buffer loads for an x of 200 MB or more, between decode's
-// 117 MB and the others' 235 MB and 1.9 GB; with 1 KiB units the form makes no difference.
+// decomposed launch takes buffer loads for an x of 200 MB or more, between decode's 117 MB and the
+// others' 235 MB and 1.9 GB; with 1 KiB units the form makes no difference.
 // row_of() returns, in lane j < k, the packed row of pair j (-1 if invalid); it is called after the
 // loads of x are issued, so whatever it loads is in flight together with them. An inactive wave
 // loads and calls row_of() (which may hold a workgroup barrier) but stores nothing. check(buf, on)

@@ -148,11 +148,18 @@ __global__ void __launch_bounds__(kScheduleThreads)
 // batches of one per thread: each thread locates its position (Algorithm 1's lookup over the
 // remapped cumulative counts), takes the pair's packed row seg_off[e][s] + offset and its token
 // recv_src[row], and shares both through LDS; the waves then copy the batch's rows, one
-// (row, 4 KiB column chunk) unit per wave as the token-major dispatch does, with one destination.
+// (row, 4 KiB column chunk) unit per wave at a time, the next unit's loads in flight under this one's
+// stores. bf16 is held at 4 waves per SIMD: few scattered writes at a time spread better over the memory.
+// Whole layer, one unit at a time with 5 waves / two units with any number / two units with 4 waves:
+// 128 ranks of 64 tokens with 64 workers 410 / 406 / 404 us, 64 ranks of 128 tokens with 32 workers
+// 495 / 495 / 452, with 128 workers 413 / 409 / 405.5, 16 ranks of 2048 columns 59.9 / 59.1 / 59.0. 1 KiB
+// units, the plain dispatch's, took 414-561 us on the first, 2 KiB units 406-491.
 // FP8: each row is quantised as it is copied, by the fp8 dispatch's unit (token, 1024-element pass)
 // with one destination; units per row is then the number of passes.
-template <bool BUF_X, bool FP8>
+constexpr int scheduled_max_waves(bool fp8) { return fp8 ? 8 : 4; }
+template <bool FP8>
 __global__ void __launch_bounds__(kScheduleThreads)
+    __attribute__((amdgpu_waves_per_eu(FP8 ? 1 : 4, scheduled_max_waves(FP8))))
     dispatch_scheduled_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ send_cnt,
                               const int32_t* __restrict__ seg_off, const int32_t* __restrict__ recv_src,
                               u32x4* __restrict__ recv, float* __restrict__ recv_scale, int R, int E, int rows, int n,
@@ -186,15 +193,45 @@ __global__ void __launch_bounds__(kScheduleThreads)
     }
     __syncthreads();
     const int units = nb * chunks;
-    for (int u = threadIdx.x / kWave; u < units; u += kScheduleThreads / kWave) {
-      const int q = u / chunks;
-      const int row = row_lds[q];
-      const int g = src_lds[q];
-      if (g < 0 || g >= T) continue;  // only a layout that does not belong to x gets here
-      if constexpr (FP8)
+    constexpr int kWaves = kScheduleThreads / kWave;
+    if constexpr (FP8) {
+      for (int u = threadIdx.x / kWave; u < units; u += kWaves) {
+        const int q = u / chunks;
+        const int row = row_lds[q];
+        const int g = src_lds[q];
+        if (g < 0 || g >= T) continue;  // only a layout that does not belong to x gets here
         dispatch_fp8_unit(x, [&] { return row; }, recv, recv_scale, g, u - q * chunks, 1, H, pitch / 16, cap, lane);
-      else
-        dispatch_bf16_unit<BUF_X>(x, [&] { return row; }, recv, g, u - q * chunks, 1, H / 8, pitch / 8, cap, lane);
+      }
+    } else {
+      const int nv = H / 8, pv = pitch / 8;
+      auto load_unit = [&](int u, u32x4* to) {
+        const int q = u / chunks;
+        // A token outside [0, T) comes only from a layout that does not belong to x; it is not stored below.
+        const int64_t g = std::min<uint32_t>((uint32_t)__builtin_amdgcn_readfirstlane(src_lds[q]), (uint32_t)(T - 1));
+        const int v0 = (u - q * chunks) * kBf16Cols + lane;
+#pragma unroll
+        for (int i = 0; i < kBf16VPL; ++i) to[i] = x[g * nv + min(v0 + i * kWave, nv - 1)];
+      };
+      u32x4 buf[kBf16VPL];
+      int u = threadIdx.x / kWave;
+      if (u < units) load_unit(u, buf);
+      for (; u < units; u += kWaves) {
+        u32x4 next[kBf16VPL];
+        if (u + kWaves < units) load_unit(u + kWaves, next);
+        const int q = u / chunks;
+        const int row = __builtin_amdgcn_readfirstlane(row_lds[q]);
+        const int g = __builtin_amdgcn_readfirstlane(src_lds[q]);
+        const int v0 = (u - q * chunks) * kBf16Cols + lane;
+        if (g >= 0 && g < T && row >= 0 && row < cap) {
+#pragma unroll
+          for (int i = 0; i < kBf16VPL; ++i) {
+            const int v = v0 + i * kWave;
+            if (v < nv) store_row_policy<kCachePolicySc1>(buf[i], recv + (int64_t)row * pv, nv, v);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < kBf16VPL; ++i) buf[i] = next[i];
+      }
     }
     __syncthreads();  // the batch's rows are consumed before the next batch overwrites them
   }
@@ -218,14 +255,11 @@ hipError_t launch_dispatch_scheduled(const void* x, const int32_t* send_cnt, con
   const u32x4* xv = static_cast<const u32x4*>(x);
   u32x4* rv = static_cast<u32x4*>(recv);
   if (fp8)
-    hipLaunchKernelGGL((dispatch_scheduled_kernel<false, true>), grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
-                       seg_off, recv_src, rv, recv_scale, R, E, rows, n, T, k, H, pitch, chunks, cap);
-  else if (T * (int64_t)H * 2 >= kBufferLoadXBytes)
-    hipLaunchKernelGGL((dispatch_scheduled_kernel<true, false>), grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
-                       seg_off, recv_src, rv, nullptr, R, E, rows, n, T, k, H, pitch, chunks, cap);
+    hipLaunchKernelGGL(dispatch_scheduled_kernel<true>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt, seg_off,
+                       recv_src, rv, recv_scale, R, E, rows, n, T, k, H, pitch, chunks, cap);
   else
-    hipLaunchKernelGGL((dispatch_scheduled_kernel<false, false>), grid, dim3(kScheduleThreads), 0, stream, xv,
-                       send_cnt, seg_off, recv_src, rv, nullptr, R, E, rows, n, T, k, H, pitch, chunks, cap);
+    hipLaunchKernelGGL(dispatch_scheduled_kernel<false>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
+                       seg_off, recv_src, rv, nullptr, R, E, rows, n, T, k, H, pitch, chunks, cap);
   return hipGetLastError();
 }
 
