@@ -229,10 +229,10 @@ int epl_decomposed_plan(const epl_config *cfg, int32_t count_groups, int32_t *gr
 /* One MoE layer in ONE launch, with identity experts: layout, dispatch, and the combine of the
  * dispatched rows (the combine reads recv itself), the combine synchronised with the dispatch per
  * row by Sentinel Polling (Data-as-Flag; Sentinel Polling variant) instead of a kernel boundary.
- * Count and send workgroups work as in epl_layout_dispatch_decomposed; combine workgroups wait for
- * the offsets, work out each token's rows, and load each 16-byte piece of a row with device-scope
- * loads until none of its elements is EPL_SENTINEL_BF16, fold it (the arithmetic of epl_combine,
- * bit for bit), and write the sentinel back over it (the reset after consumption).
+ * Count and send workgroups work as in epl_layout_dispatch_decomposed; then every workgroup
+ * combines: it works out each token's rows, loads each 16-byte piece of a row with device-scope
+ * loads until none of its elements is EPL_SENTINEL_BF16, folds it (the arithmetic of epl_combine,
+ * bit for bit), and writes the sentinel back over it (the reset after consumption).
  *   recv       recv_rows_cap rows of pitch bf16 elements: elements 0..H-1 of every row must hold
  *              EPL_SENTINEL_BF16 before the first call (epl_sentinel_fill over the whole buffer);
  *              each call leaves them so. No other call may write them in between.

@@ -10,7 +10,8 @@
 //     again; the last one publishes the ready word. They then write the expert, rank and segment
 //     offsets (one slice each);
 //   * send workgroups [nc, grid) issue the loads of their first tokens, wait for the ready word,
-//     and then place and send rows exactly as the fused row kernel does, striding over the units.
+//     and then place and send batches of tokens, striding over them;
+//   * in the layer variants every workgroup then combines (Data-as-Flag, below).
 // The count/send split nc is the knob the paper sizes by its latency model (count cores in
 // proportion to the experts and inversely to the token load).
 //
@@ -41,6 +42,8 @@ constexpr int kSyncScan = 1 * kSyncStride;    // count workgroups done with thei
 constexpr int kSyncReady = 2 * kSyncStride;   // 1 once every offset the send role reads is published
 constexpr int kSyncExit = 3 * kSyncStride;    // workgroups done
 constexpr int kSyncStatus = 4 * kSyncStride;  // give-up bits of this launch
+// Words of every line that the workgroups count at on their way to a counter above (workgroup_publish).
+constexpr int kLeafHist = 8, kLeafExit = 16, kNoLeaf = 0;
 constexpr int kGaveUpCount = 1;    // a count workgroup stopped waiting
 constexpr int kGaveUpSend = 2;     // a send workgroup stopped waiting
 constexpr int kGaveUpCombine = 4;  // a combine wave stopped waiting for a row
@@ -63,12 +66,13 @@ struct DecomposedArgs {
   u32x4* out;                  // [T][H] bf16
   uint64_t* marks;             // Token-Flag Fusion and Data-for-Checksum: [cap][cchunks] words, one per 1 KiB
   uint64_t epoch;              // this call's epoch: the flag value, or the checksum's salt
-  int cchunks, nco;            // 1 KiB column chunks per row; combine workgroups
+  int cchunks, crun;           // 1 KiB column chunks per row, and per combine task
+  int batch;                   // tokens a send workgroup takes at a time, <= kWavesPerBlock
   const u32x4* x;
   u32x4* recv;
-  int nv, pv, chunks;          // x row and recv pitch in 16-byte vectors; 4 KiB chunks per row
+  int nv, pv;                  // x row and recv pitch in 16-byte vectors
   int64_t cap;
-  int nc, ns;                  // count and send workgroups
+  int nc, ns;                  // count workgroups; workgroups that send (all, where the count workgroups join)
   int32_t* sync;               // [kSyncWords]
   int32_t* status;             // the call's wait status
   int64_t spin_ticks;
@@ -77,14 +81,20 @@ struct DecomposedArgs {
 
 // Polls `word` with device-scope loads until it reaches `target` or `limit` ticks of the 100 MHz
 // real-time clock pass. Every lane of the wave runs it with the same values.
+// SLEEP: 64-cycle steps between polls.
+template <int SLEEP>
 __device__ __forceinline__ bool wait_at_least(int32_t* word, int target, int64_t limit) {
   const int64_t t0 = wall_clock64();
   while (ld32<true>(word) < target) {
     if (wall_clock64() - t0 > limit) return false;
-    __builtin_amdgcn_s_sleep(2);
+    __builtin_amdgcn_s_sleep(SLEEP);
   }
   return true;
 }
+
+// The count workgroups wait for each other and poll often; the send workgroups, four times as many, wait
+// for all of it, and their polls go to the memory channel that the counters sit in.
+constexpr int kSleepCount = 2, kSleepReady = 8;
 
 // The whole workgroup waits: thread 0 polls, the others park at the barrier. With ACQUIRE, thread
 // 0 then takes a device-scope acquire (it invalidates the compute unit's L1 and the XCD's L2 of
@@ -93,7 +103,7 @@ __device__ __forceinline__ bool wait_at_least(int32_t* word, int target, int64_t
 template <bool ACQUIRE = false>
 __device__ __forceinline__ bool workgroup_wait(int32_t* word, int target, int64_t limit, int32_t* flag) {
   if (threadIdx.x == 0) {
-    const bool ok = wait_at_least(word, target, limit);
+    const bool ok = wait_at_least<ACQUIRE ? kSleepReady : kSleepCount>(word, target, limit);
     if (ACQUIRE && ok) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     *flag = ok ? 1 : 0;
   }
@@ -103,14 +113,25 @@ __device__ __forceinline__ bool workgroup_wait(int32_t* word, int target, int64_
   return ok;
 }
 
-// Every thread waits for its own stores to complete; then thread 0 adds one to `counter` and
-// returns the count before its add (in thread 0 only).
-__device__ __forceinline__ int workgroup_publish(int32_t* counter) {
+// Counts workgroup i of n at the counter `root`, once the workgroup's own stores are complete; true in
+// thread 0 of the last one. Adds to one address are served one after another, so where all workgroups
+// arrive together they add to kLeaves words (word `leaf` of each synchronisation line) and the last of
+// each leaf adds to the root: the counts of 256 workgroups meet 3-4 us after the last has finished, 6-7
+// with one counter. With kNoLeaf they add to the root (arrivals spread by more than an add takes: the
+// second level would only cost its round trip, 3 us).
+constexpr int kLeaves = kSyncWords / kSyncStride;
+__device__ __forceinline__ int leaf_count(int n) { return min(n, kLeaves); }
+__device__ __forceinline__ bool workgroup_publish(int32_t* sync, int root, int leaf, int i, int n) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  int before = -1;
-  if (threadIdx.x == 0) before = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return before;
+  if (threadIdx.x != 0) return false;
+  auto add = [&](int word) {
+    return __hip_atomic_fetch_add(&sync[word], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (leaf == kNoLeaf) return add(root) == n - 1;
+  const int l = i % kLeaves;
+  if (add(l * kSyncStride + leaf) != (n - l + kLeaves - 1) / kLeaves - 1) return false;
+  return add(root) == leaf_count(n) - 1;
 }
 
 __device__ __forceinline__ void count_role(const DecomposedArgs& A, int i, int32_t* lds, int32_t* red,
@@ -120,91 +141,28 @@ __device__ __forceinline__ void count_role(const DecomposedArgs& A, int i, int32
     hist_chunk<true>(G, b, A.F.idx, A.tok_nranks, A.chunk_e, A.chunk_r, A.inval, A.fmask, lds, red, A.cnt);
     __syncthreads();  // the next chunk reuses the LDS
   }
-  workgroup_publish(&A.sync[kSyncHist]);
-  if (!workgroup_wait(&A.sync[kSyncHist], A.nc, A.spin_ticks, flag) && threadIdx.x == 0)
+  workgroup_publish(A.sync, kSyncHist, kLeafHist, i, A.nc);
+  if (!workgroup_wait(&A.sync[kSyncHist], leaf_count(A.nc), A.spin_ticks, flag) && threadIdx.x == 0)
     atomicOr(&A.sync[kSyncStatus], kGaveUpCount);
   for (int item = i; item < G.E + G.R + 1; item += A.nc) {
     scan_item<true>(G, item, A.chunk_e, A.chunk_r, A.inval, A.recv_cnt, A.send_cnt, A.rank_cnt, A.seg_rel,
                     A.num_invalid, scratch, seg_start, A.cnt);
     __syncthreads();
   }
-  const int before = workgroup_publish(&A.sync[kSyncScan]);
-  if (threadIdx.x == 0 && before == A.nc - 1) {
+  if (workgroup_publish(A.sync, kSyncScan, kNoLeaf, i, A.nc)) {
     // Every count workgroup's stores completed before its count; publish the offsets.
     __hip_atomic_store(&A.sync[kSyncReady], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // expert_off, rank_off and one slice of seg_off, from the published totals.
-  if (workgroup_wait(&A.sync[kSyncReady], 1, A.spin_ticks, flag))
+  if (workgroup_wait(&A.sync[kSyncReady], 1, A.spin_ticks, flag)) {
     fused_meta_block<true>(A.F, i, A.nc, lds);
-  else if (threadIdx.x == 0)
-    atomicOr(&A.sync[kSyncStatus], kGaveUpCount);
-}
-
-__device__ __forceinline__ bool holds_sentinel(u32x4 v);
-
-// Places and sends the units j * 4, j * 4 + 4 * ns, ... (4 per workgroup, one per wave), as the
-// fused row kernel does, after waiting for the offsets once the first unit's loads are issued.
-// Measured against handing out batches of units from a launch-wide counter, with the count
-// workgroups joining once their counting was done: that was slower (decode 416.7 against
-// 396.8 us per layer, the Qwen3-30B shape 61.2 against 50.7 us), the counter's atomics serialising.
-template <int SYNC>
-__device__ __forceinline__ void publish_marks(const DecomposedArgs& A, const u32x4* buf, const bool* on, int my_row,
-                                              int c, int k, int lane);
-
-template <bool BUF_X, int SYNC>
-__device__ __forceinline__ void send_role(const DecomposedArgs& A, int j, int32_t* lds, int32_t* flag) {
-  const int lane = threadIdx.x % kWave;
-  const int w = threadIdx.x / kWave;
-  const int k = A.F.G.k;
-  int32_t* rows_lds = lds;  // [kWavesPerBlock][k]
-  int32_t* hist = lds + kWavesPerBlock * EPL_MAX_TOPK + w * (A.F.G.E + A.F.G.R);
-  const int64_t units = A.F.G.T * A.chunks;
-  const int64_t stride = (int64_t)A.ns * kWavesPerBlock;
-  bool waited = false, gave_up = false;
-  // The loop bound depends on the workgroup's first unit only, so every wave runs the same
-  // iterations and reaches the same barriers.
-  for (int64_t ub = (int64_t)j * kWavesPerBlock; ub < units && !gave_up; ub += stride) {
-    const int64_t g_first = ub / A.chunks;
-    const int64_t g_last = std::min(units - 1, ub + kWavesPerBlock - 1) / A.chunks;
-    const int64_t u = ub + w;
-    const bool active = u < units;
-    const int64_t g = (active ? u : units - 1) / A.chunks;
-    const int c = (int)((active ? u : units - 1) - g * A.chunks);
-    dispatch_bf16_unit<BUF_X>(
-        A.x,
-        [&] {
-          if (!waited) {  // the first unit's loads of x are in flight while the offsets arrive
-            waited = true;
-            gave_up = !workgroup_wait<true>(&A.sync[kSyncReady], A.ready_target, A.spin_ticks, flag);
-            if (gave_up && threadIdx.x == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpSend);
-          }
-          if (gave_up) return -1;  // uniform over the workgroup: nothing is stored
-          if (w <= g_last - g_first) {
-            const int r = token_rows<false>(A.F, g_first + w, true, hist, lane);
-            if (lane < k) rows_lds[w * k + lane] = r;
-          }
-          __syncthreads();
-          const int r = lane < k ? rows_lds[(g - g_first) * k + lane] : -1;
-          __syncthreads();  // every wave has its rows before the next iteration rewrites them
-          return r;
-        },
-        A.recv, g, c, k, A.nv, A.pv, A.cap, lane, active,
-        [&](const u32x4* buf, const bool* on) {
-          if constexpr (SYNC == kDafSentinel) {
-            bool seen = false;
-#pragma unroll
-            for (int q = 0; q < kBf16VPL; ++q) seen |= on[q] && holds_sentinel(buf[q]);
-            if (__ballot(seen) != 0 && lane == 0) atomicOr(&A.sync[kSyncStatus], kSentinelInX);
-          }
-        },
-        [&](const u32x4* buf, const bool* on, int my_row) {
-          if constexpr (SYNC == kDafFlag || SYNC == kDafChecksum) publish_marks<SYNC>(A, buf, on, my_row, c, k, lane);
-        });
+  } else {
+    if (threadIdx.x == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCount);
   }
 }
 
 // ------------------------------------------------------------------------ Sentinel Polling
-// The layer variant adds combine workgroups that gather the dispatched rows (identity experts:
+// In the layer variant the workgroups go on to gather the dispatched rows (identity experts:
 // the combine reads the receive buffer itself) while the send workgroups are still writing them,
 // with no barrier in between: the paper's Sentinel Polling (Data-as-Flag). Every receive row holds
 // the reserved bf16 pattern EPL_SENTINEL_BF16 (a negative NaN with every payload bit set, which
@@ -223,26 +181,6 @@ __device__ __forceinline__ bool holds_sentinel(u32x4 v) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) any |= ((v[i] & 0xFFFFu) == 0xFFFFu) | ((v[i] >> 16) == 0xFFFFu);
   return any;
-}
-
-// Device-scope 16-byte load and store of vector v of a row of nv vectors.
-__device__ __forceinline__ u32x4 load_vec_dev(const u32x4* row, int nv, int v) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(row), 0, nv * 16, kBufferRsrcWord3);
-  return __builtin_amdgcn_raw_buffer_load_b128(r, v * 16, 0, kCachePolicySc1);
-}
-
-// Loads lane's vector v of `row` until no lane of the wave sees a sentinel in its vector, or
-// `limit` ticks pass (false). The loop condition is wave-uniform.
-__device__ __forceinline__ bool poll_vec(const u32x4* row, int nv, int v, u32x4& val, int64_t limit) {
-  val = load_vec_dev(row, nv, v);
-  if (__ballot(holds_sentinel(val)) == 0) return true;
-  const int64_t t0 = wall_clock64();
-  while (true) {
-    __builtin_amdgcn_s_sleep(1);
-    if (holds_sentinel(val)) val = load_vec_dev(row, nv, v);
-    if (__ballot(holds_sentinel(val)) == 0) return true;
-    if (wall_clock64() - t0 > limit) return false;
-  }
 }
 
 // ------------------------------------------------------------------------ Token-Flag Fusion, Data-for-Checksum
@@ -296,185 +234,297 @@ __device__ __forceinline__ uint64_t wave_xor64(uint64_t h) {
 
 __device__ __forceinline__ uint64_t epoch_salt(uint64_t epoch) { return mix64(epoch ^ 0x5851F42D4C957F2Dull); }
 
-// After a send wave's stores of unit (token, 4 KiB chunk c): the marks of the kBf16VPL 1 KiB
-// chunks it wrote, for each of the token's destination rows (my_row in lanes 0..k-1).
+// Sends the batches j, j + ns, ... of A.batch consecutive tokens, after waiting for the offsets once
+// the first loads are issued. One wave places each token of the batch (its rows go to the others
+// through LDS), then the four waves take the batch's (token, 1 KiB column chunk) units in turn. A token
+// is placed once, and rows are written in the 1 KiB pieces that spread best over the memory. A wave
+// loads kSendAhead units together: waiting for a load that was issued behind stores is waiting for
+// those stores. Returns false if it gave up.
+// Against one 4 KiB unit per wave at a time, each with a placement of its own, whole layer: 16 ranks x
+// 128 tokens x 2048 columns 49.0 -> 44.9 us, 32 x 64 x 7168 113.0 -> 107.8, 64 x 128 x 7168 411 -> 408.
+// With two units loaded together 47.1, 116 and 413 (at three workgroups per compute unit; four units
+// there 45.0, 112, 412); with the next unit's load in flight under the stores 51, 125 and 410.
+// Measured against handing out batches of units from a launch-wide counter, with the count
+// workgroups joining once their counting was done: that was slower (decode 416.7 against
+// 396.8 us per layer, the Qwen3-30B shape 61.2 against 50.7 us), the counter's atomics serialising.
+constexpr int kSendAhead = 4;
 template <int SYNC>
-__device__ __forceinline__ void publish_marks(const DecomposedArgs& A, const u32x4* buf, const bool* on, int my_row,
-                                              int c, int k, int lane) {
-  uint64_t val[kBf16VPL];
-  if constexpr (SYNC == kDafChecksum) {
-    const uint64_t salt = epoch_salt(A.epoch);
+__device__ __forceinline__ bool send_role(const DecomposedArgs& A, int j, int32_t* lds, int32_t* flag) {
+  const int lane = threadIdx.x % kWave;
+  const int w = threadIdx.x / kWave;
+  const int k = A.F.G.k;
+  const int nv = A.nv;
+  int32_t* rows_lds = lds;  // [kWavesPerBlock][k]
+  int32_t* hist = lds + kWavesPerBlock * EPL_MAX_TOPK + w * (A.F.G.E + A.F.G.R);
+  const uint64_t salt = epoch_salt(A.epoch);
+  bool waited = false;
+  // The loop bounds are the workgroup's, so every wave reaches the same barriers.
+  for (int64_t g0 = (int64_t)j * A.batch; g0 < A.F.G.T; g0 += (int64_t)A.ns * A.batch) {
+    const int ntok = (int)std::min<int64_t>(A.batch, A.F.G.T - g0);  // <= kWavesPerBlock
+    const int units = ntok * A.cchunks;
+    u32x4 buf[kSendAhead];
+    auto load_units = [&](int u0) {  // units u0, u0 + 4, ... of this wave; no branch, past the last an empty resource
 #pragma unroll
-    for (int u = 0; u < kBf16VPL; ++u) val[u] = wave_xor64(lane_hash(buf[u], on[u], lane)) ^ salt;
-  } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's device-scope row stores are complete
+      for (int q = 0; q < kSendAhead; ++q) {
+        const int u = min(u0 + q * kWavesPerBlock, units - 1);
+        const int tl = u / A.cchunks;
+        const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<u32x4*>(A.x + (g0 + tl) * nv), 0, u0 + q * kWavesPerBlock < units ? nv * 16 : 0, kBufferRsrcWord3);
+        buf[q] = __builtin_amdgcn_raw_buffer_load_b128(xs, ((u - tl * A.cchunks) * kWave + lane) * 16, 0, 0);
+      }
+    };
+    load_units(w);
+    if (!waited) {
+      waited = true;
+      if (!workgroup_wait<true>(&A.sync[kSyncReady], A.ready_target, A.spin_ticks, flag)) {
+        if (threadIdx.x == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpSend);
+        return false;  // uniform over the workgroup: nothing is stored
+      }
+    }
+    if (w < ntok) {
+      const int r = token_rows<false>(A.F, g0 + w, true, hist, lane);
+      if (lane < k) rows_lds[w * k + lane] = r;
+    }
+    __syncthreads();
+    for (int u0 = w; u0 < units; u0 += kSendAhead * kWavesPerBlock) {
+      if (u0 != w) load_units(u0);
 #pragma unroll
-    for (int u = 0; u < kBf16VPL; ++u) val[u] = A.epoch;
+      for (int q = 0; q < kSendAhead; ++q) {
+        const int u = u0 + q * kWavesPerBlock;
+        if (u >= units) break;
+        const int tl = u / A.cchunks;
+        const int c = u - tl * A.cchunks;
+        const int v = c * kWave + lane;
+        const int my_row = lane < k ? rows_lds[tl * k + lane] : -1;
+        if constexpr (SYNC == kDafSentinel) {
+          if (__ballot(v < nv && holds_sentinel(buf[q])) != 0 && lane == 0)
+            atomicOr(&A.sync[kSyncStatus], kSentinelInX);
+        }
+        for (int jj = 0; jj < k; ++jj) {
+          const int row = __builtin_amdgcn_readlane(my_row, jj);
+          if (row < 0 || row >= A.cap) continue;
+          if (v < nv) store_row_policy<kCachePolicySc1>(buf[q], A.recv + (int64_t)row * A.pv, nv, v);
+        }
+        if constexpr (SYNC == kDafChecksum) {
+          const uint64_t m = wave_xor64(lane_hash(buf[q], v < nv, lane)) ^ salt;
+          if (my_row >= 0 && my_row < A.cap) st64_dev(&A.marks[(int64_t)my_row * A.cchunks + c], m);
+        }
+      }
+    }
+    if constexpr (SYNC == kDafFlag) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's device-scope row stores are complete
+      for (int u = w; u < units; u += kWavesPerBlock) {
+        const int tl = u / A.cchunks;
+        const int my_row = lane < k ? rows_lds[tl * k + lane] : -1;
+        if (my_row >= 0 && my_row < A.cap) st64_dev(&A.marks[(int64_t)my_row * A.cchunks + u - tl * A.cchunks], A.epoch);
+      }
+    }
+    __syncthreads();  // every wave has read the rows before the next batch rewrites them
   }
-  // Index i = j * kBf16VPL + u names destination j's chunk u; lanes take them in rounds of 64.
-  for (int base = 0; base < k * kBf16VPL; base += kWave) {
-    const int i = base + lane;
-    const int j = i / kBf16VPL, u = i % kBf16VPL;
-    const int row = __shfl(my_row, j < k ? j : 0, kWave);
-    uint64_t m = val[0];
-#pragma unroll
-    for (int q = 1; q < kBf16VPL; ++q) m = u == q ? val[q] : m;
-    const int cc = c * kBf16VPL + u;
-    if (j < k && row >= 0 && row < A.cap && cc < A.cchunks) st64_dev(&A.marks[(int64_t)row * A.cchunks + cc], m);
-  }
-}
-
-// Token-Flag Fusion: polls the chunk's mark until it holds the epoch, then loads the lane's vector.
-// The loop condition is wave-uniform (one mark per wave).
-__device__ __forceinline__ bool poll_flag(const uint64_t* mark, uint64_t epoch, const u32x4* row, int nv, int v,
-                                          u32x4& val, int64_t limit) {
-  if (ld64_dev(mark) != epoch) {
-    const int64_t t0 = wall_clock64();
-    do {
-      if (wall_clock64() - t0 > limit) return false;
-      __builtin_amdgcn_s_sleep(1);
-    } while (ld64_dev(mark) != epoch);
-  }
-  val = load_vec_dev(row, nv, v);
   return true;
 }
 
-// Data-for-Checksum: loads the lane's vector and the chunk's mark until the salted hash of the
-// wave's loaded chunk equals the mark. The comparison is wave-uniform.
-__device__ __forceinline__ bool poll_checksum(const uint64_t* mark, uint64_t salt, const u32x4* row, int nv, int v,
-                                              bool on, int lane, u32x4& val, int64_t limit) {
-  int64_t t0 = -1;
-  while (true) {
-    const uint64_t m = ld64_dev(mark);
-    val = load_vec_dev(row, nv, v);
-    if ((wave_xor64(lane_hash(val, on, lane)) ^ salt) == m) return true;
-    if (t0 < 0)
-      t0 = wall_clock64();
-    else if (wall_clock64() - t0 > limit)
-      return false;
-    __builtin_amdgcn_s_sleep(1);
-  }
+// Loads vector v of packed row `row` (nothing, and zeros, for row < 0: its resource is empty).
+__device__ __forceinline__ u32x4 gather_vec(const u32x4* y, int row, int pv, int nv, int v) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(y + (int64_t)max(row, 0) * pv), 0,
+                                                                     row >= 0 ? nv * 16 : 0, kBufferRsrcWord3);
+  return __builtin_amdgcn_raw_buffer_load_b128(r, v * 16, 0, kCachePolicySc1);
 }
 
-// Combine units (token g, 1 KiB column chunk c): one wave per unit, waves iterating on their own.
-// Each wave works out its token's rows as the send role does (no metadata written), then folds
-// the valid rows in j order, acc = fmaf(w_j, y_j, acc) from +0, bf16 round-to-nearest-even, as
-// the combine kernel does.
+// Combine tasks (token g, a run of 1 KiB column chunks): one wave per task, waves iterating on their
+// own. Each wave works out its token's rows as the send role does (no metadata written), then for
+// each chunk gathers the valid rows and folds them in j order, acc = fmaf(w_j, y_j, acc) from +0,
+// bf16 round-to-nearest-even, as the combine kernel does.
+//
+// What bounds it is latency: a row's load is a round trip to memory (device-scope, past the L2), and
+// placing a token costs about as much again. So all of a chunk's rows (up to kAhead at a time) are
+// loaded before any is checked, a wave keeps its token for as many chunks as leave every wave a task, and
+// every workgroup of the launch combines. Against combine workgroups of their own that loaded one row after
+// another, whole layer: 16 ranks x 128 tokens x 2048 columns sentinel 68.9 -> 55.1 us, flag 75.4 -> 46.5,
+// checksum 75.4 -> 60.0; 32 x 64 x 7168 sentinel 192 -> 156; 64 x 128 x 7168 967 -> 630.
 template <int SYNC>
-__device__ __forceinline__ void combine_role(const DecomposedArgs& A, int ci, int32_t* lds, int32_t* flag) {
+__device__ __forceinline__ void combine_role(const DecomposedArgs& A, int ci, int32_t* lds) {
+  constexpr int kAhead = 8;
   const Geom& G = A.F.G;
   const int lane = threadIdx.x % kWave;
   const int w = threadIdx.x / kWave;
   const int k = G.k;
   int32_t* hist = lds + kWavesPerBlock * EPL_MAX_TOPK + w * (G.E + G.R);
-  if (!workgroup_wait<true>(&A.sync[kSyncReady], A.ready_target, A.spin_ticks, flag)) {
-    if (threadIdx.x == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
-    return;
-  }
   const int nv = A.nv;
-  const int64_t units = G.T * A.cchunks;
-  const int64_t stride = (int64_t)A.nco * kWavesPerBlock;
+  const int runs = (A.cchunks + A.crun - 1) / A.crun;  // per token
+  const int64_t tasks = G.T * runs;
+  const int64_t stride = (int64_t)gridDim.x * kWavesPerBlock;
   const u32x4* y = A.recv;
   const uint64_t salt = epoch_salt(A.epoch);
-  for (int64_t u = (int64_t)ci * kWavesPerBlock + w; u < units; u += stride) {
-    const int64_t g = u / A.cchunks;
-    const int c = (int)(u - g * A.cchunks);
+  bool arrived = true;
+  for (int64_t u = (int64_t)ci * kWavesPerBlock + w; u < tasks && arrived; u += stride) {
+    const int64_t g = u / runs;
+    const int c0 = (int)(u - g * runs) * A.crun;
+    const int c1 = min(c0 + A.crun, A.cchunks);
+    const int wbits = __builtin_bit_cast(int, A.topk_w[g * k + min(lane, k - 1)]);
     const int rows = token_rows<false>(A.F, g, false, hist, lane);
-    const int v = c * kWave + lane;
-    const bool on = v < nv;
-    const int vl = min(v, nv - 1);
-    float acc[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-    bool arrived = true;
-    for (int j = 0; j < k; ++j) {
-      const int row = __builtin_amdgcn_readlane(rows, j);
-      if (row < 0) continue;
-      const float wj = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(
-                                                      __builtin_bit_cast(int, A.topk_w[g * k + j])));
-      const u32x4* yr = y + (int64_t)row * A.pv;
-      u32x4 val;
-      bool got;
-      if constexpr (SYNC == kDafFlag)
-        got = poll_flag(A.marks + (int64_t)row * A.cchunks + c, A.epoch, yr, nv, vl, val, A.spin_ticks);
-      else if constexpr (SYNC == kDafChecksum)
-        got = poll_checksum(A.marks + (int64_t)row * A.cchunks + c, salt, yr, nv, vl, on, lane, val, A.spin_ticks);
-      else
-        got = poll_vec(yr, nv, vl, val, A.spin_ticks);
-      if (!got) {
-        arrived = false;
-        break;
+    int c = c0;
+    for (; c < c1; ++c) {
+      const int v = c * kWave + lane;
+      const bool on = v < nv;
+      const int vl = min(v, nv - 1);
+      // Lane j's mark of this chunk (Token-Flag Fusion, Data-for-Checksum).
+      const uint64_t* mark = A.marks + (int64_t)max(rows, 0) * A.cchunks + c;
+      if constexpr (SYNC == kDafFlag) {  // every row's chunk is there before any is loaded
+        int64_t t0 = -1;
+        while (__ballot(rows >= 0 && ld64_dev(mark) != A.epoch) != 0) {
+          if (t0 < 0) t0 = wall_clock64();
+          if (wall_clock64() - t0 > A.spin_ticks) {
+            arrived = false;
+            break;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        }
+        if (!arrived) break;  // wave-uniform, as is every exit below
       }
+      float acc[8];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        acc[2 * i] = fmaf(wj, bf16lo_to_f32(val[i]), acc[2 * i]);
-        acc[2 * i + 1] = fmaf(wj, bf16hi_to_f32(val[i]), acc[2 * i + 1]);
+      for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+      for (int j0 = 0; j0 < k && arrived; j0 += kAhead) {
+        u32x4 buf[kAhead];
+        int row[kAhead];
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+          row[q] = __builtin_amdgcn_readlane(rows, j0 + q);  // -1 in the lanes past k (k <= 32)
+          buf[q] = gather_vec(y, row[q], A.pv, nv, vl);
+        }
+        if constexpr (SYNC != kDafFlag) {
+          auto load_mark = [&] { return SYNC == kDafChecksum && rows >= 0 ? ld64_dev(mark) : 0; };
+          uint64_t m = load_mark();
+          // Whether every lane's part of choice jj's chunk, loaded as val, has arrived.
+          auto is_there = [&](u32x4 val, int jj) {
+            if constexpr (SYNC == kDafChecksum) {
+              const uint64_t mj = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)m, jj) |
+                                  (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(m >> 32), jj) << 32;
+              return __ballot((wave_xor64(lane_hash(val, on, lane)) ^ salt) != mj) == 0;
+            }
+            return __ballot(holds_sentinel(val)) == 0;
+          };
+          int64_t t0 = -1;
+          while (true) {
+            uint32_t missing = 0;  // bit q: choice j0 + q has not arrived
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q)
+              if (row[q] >= 0 && !is_there(buf[q], j0 + q)) missing |= 1u << q;
+            if (missing == 0) break;
+            // Poll one missing row until it is there (eight polled at once slow the sends down), then
+            // load all that were missing again (keeping the polled value costs registers and was no faster).
+            const int jp = j0 + __builtin_ctz(missing);
+            const int rp = __builtin_amdgcn_readlane(rows, jp);
+            if (t0 < 0) t0 = wall_clock64();
+            do {
+              if (wall_clock64() - t0 > A.spin_ticks) {
+                arrived = false;
+                break;
+              }
+              __builtin_amdgcn_s_sleep(4);
+              m = load_mark();
+            } while (!is_there(gather_vec(y, rp, A.pv, nv, vl), jp));
+            if (!arrived) break;
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q)
+              if ((missing >> q) & 1u) buf[q] = gather_vec(y, row[q], A.pv, nv, vl);
+            m = load_mark();
+          }
+          if (!arrived) break;
+        }
+#pragma unroll
+        for (int q = 0; q < kAhead; ++q) {
+          if (row[q] < 0) continue;
+          const float wj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(wbits, j0 + q));
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            acc[2 * i] = fmaf(wj, bf16lo_to_f32(buf[q][i]), acc[2 * i]);
+            acc[2 * i + 1] = fmaf(wj, bf16hi_to_f32(buf[q][i]), acc[2 * i + 1]);
+          }
+        }
       }
-      if (SYNC == kDafSentinel && on) {  // consumed: back to the sentinel for the next layer
-        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(yr), 0, nv * 16,
-                                                                           kBufferRsrcWord3);
-        const u32x4 s = {kSentinelPair, kSentinelPair, kSentinelPair, kSentinelPair};
-        __builtin_amdgcn_raw_buffer_store_b128(s, r, v * 16, 0, kCachePolicySc1);
+      if (!arrived) break;
+      if (on) {
+        u32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = f32x2_to_bf16x2(acc[2 * i], acc[2 * i + 1]);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(A.out + g * nv, 0, nv * 16, kBufferRsrcWord3);
+        __builtin_amdgcn_raw_buffer_store_b128(o, r, v * 16, 0, kCachePolicySc1Nt);
       }
     }
-    if (!arrived) {  // wave-uniform: stop, store nothing more
-      if (lane == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
-      break;
-    }
-    if (on) {
-      u32x4 o;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = f32x2_to_bf16x2(acc[2 * i], acc[2 * i + 1]);
-      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(A.out + g * nv, 0, nv * 16, kBufferRsrcWord3);
-      __builtin_amdgcn_raw_buffer_store_b128(o, r, v * 16, 0, kCachePolicySc1Nt);
+    if constexpr (SYNC == kDafSentinel) {
+      // What was consumed, back to the sentinel for the next layer: after the last chunk, as a load
+      // issued behind stores would wait for them.
+      const u32x4 s = {kSentinelPair, kSentinelPair, kSentinelPair, kSentinelPair};
+      for (int cr = c0; cr < c; ++cr) {
+        const int v = cr * kWave + lane;
+        for (int j = 0; j < k; ++j) {
+          const int row = __builtin_amdgcn_readlane(rows, j);
+          if (row >= 0 && v < nv) store_row_policy<kCachePolicySc1>(s, A.recv + (int64_t)row * A.pv, nv, v);
+        }
+      }
     }
   }
+  if (!arrived && lane == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
 }
 
 // The last workgroup to finish writes the status word and zeroes the synchronisation words. Every
 // other workgroup has passed all its waits by then.
 __device__ __forceinline__ void finish(const DecomposedArgs& A) {
-  const int before = workgroup_publish(&A.sync[kSyncExit]);
-  if (threadIdx.x == 0 && before == (int)gridDim.x - 1) {
+  if (workgroup_publish(A.sync, kSyncExit, kLeafExit, (int)blockIdx.x, (int)gridDim.x)) {
     st32<true>(A.status, ld32<true>(&A.sync[kSyncStatus]));
-    for (int i = 0; i < kSyncWords; i += kSyncStride) st32<true>(&A.sync[i], 0);
+    for (int i = 0; i < kSyncWords; i += kLeafHist) st32<true>(&A.sync[i], 0);
   }
 }
 
-template <bool BUF_X, int SYNC>
-__global__ void __launch_bounds__(kLayoutThreads) decomposed_kernel(DecomposedArgs A) {
+// Every workgroup of a layer variant goes on to combine when its own role is done: the whole device
+// sends first, and by the time a workgroup combines, most of what it gathers has arrived.
+template <int SYNC>
+__global__ void __launch_bounds__(kLayoutThreads) __attribute__((amdgpu_waves_per_eu(5)))
+    decomposed_kernel(DecomposedArgs A) {
   static_assert(kDispatchThreads == kLayoutThreads, "both roles run in 256-thread workgroups");
   extern __shared__ int32_t lds[];
   __shared__ int32_t red[kLayoutWaves];
   __shared__ int32_t scratch[kLayoutWaves];
   __shared__ int32_t seg_start[EPL_MAX_EXPERTS + 1];
   __shared__ int32_t flag;
-  if ((int)blockIdx.x < A.nc)
+  bool ready = true;  // the offsets are published, and acquired
+  bool sends = true;
+  int j = (int)blockIdx.x - A.nc;
+  if (j < 0) {
     count_role(A, (int)blockIdx.x, lds, red, scratch, seg_start, &flag);
-  else if (SYNC == kDafNone || (int)blockIdx.x < A.nc + A.ns)
-    send_role<BUF_X, SYNC>(A, (int)blockIdx.x - A.nc, lds, &flag);
-  else
-    combine_role<SYNC>(A, (int)blockIdx.x - A.nc - A.ns, lds, &flag);
+    sends = A.ns > (int)gridDim.x - A.nc;
+    j += (int)gridDim.x;  // after the send workgroups: gridDim - nc + i
+    if (sends || SYNC != kDafNone)
+      ready = workgroup_wait<true>(&A.sync[kSyncReady], A.ready_target, A.spin_ticks, &flag);
+  }
+  if (sends && ready) ready = send_role<SYNC>(A, j, lds, &flag);
+  if constexpr (SYNC != kDafNone) {
+    if (ready)
+      combine_role<SYNC>(A, (int)blockIdx.x, lds);
+    else if (threadIdx.x == 0)
+      atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
+  }
   finish(A);
 }
 
 // ------------------------------------------------------------------------ host
 namespace {
 
-template <bool BUF_X>
 void launch_variant(int sync, dim3 grid, dim3 block, size_t lds, hipStream_t stream, const DecomposedArgs& A) {
   switch (sync) {
     case kDafSentinel:
-      hipLaunchKernelGGL((decomposed_kernel<BUF_X, kDafSentinel>), grid, block, lds, stream, A);
+      hipLaunchKernelGGL(decomposed_kernel<kDafSentinel>, grid, block, lds, stream, A);
       break;
     case kDafFlag:
-      hipLaunchKernelGGL((decomposed_kernel<BUF_X, kDafFlag>), grid, block, lds, stream, A);
+      hipLaunchKernelGGL(decomposed_kernel<kDafFlag>, grid, block, lds, stream, A);
       break;
     case kDafChecksum:
-      hipLaunchKernelGGL((decomposed_kernel<BUF_X, kDafChecksum>), grid, block, lds, stream, A);
+      hipLaunchKernelGGL(decomposed_kernel<kDafChecksum>, grid, block, lds, stream, A);
       break;
     default:
-      hipLaunchKernelGGL((decomposed_kernel<BUF_X, kDafNone>), grid, block, lds, stream, A);
+      hipLaunchKernelGGL(decomposed_kernel<kDafNone>, grid, block, lds, stream, A);
   }
 }
 
@@ -487,51 +537,61 @@ size_t decomposed_lds_bytes(const Geom& g) {
 
 }  // namespace
 
-template <bool BUF_X, int SYNC>
+template <int SYNC>
 static hipError_t occupancy(int* per_cu, size_t lds) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, decomposed_kernel<BUF_X, SYNC>, kLayoutThreads, lds);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, decomposed_kernel<SYNC>, kLayoutThreads, lds);
 }
 
-template <bool BUF_X>
 static hipError_t occupancy_of(int sync, int* per_cu, size_t lds) {
   switch (sync) {
-    case kDafSentinel: return occupancy<BUF_X, kDafSentinel>(per_cu, lds);
-    case kDafFlag: return occupancy<BUF_X, kDafFlag>(per_cu, lds);
-    case kDafChecksum: return occupancy<BUF_X, kDafChecksum>(per_cu, lds);
-    default: return occupancy<BUF_X, kDafNone>(per_cu, lds);
+    case kDafSentinel: return occupancy<kDafSentinel>(per_cu, lds);
+    case kDafFlag: return occupancy<kDafFlag>(per_cu, lds);
+    case kDafChecksum: return occupancy<kDafChecksum>(per_cu, lds);
+    default: return occupancy<kDafNone>(per_cu, lds);
   }
 }
 
+// Send workgroups per compute unit. Scattered writes go faster from fewer waves: layout and dispatch, us
+// per layer at 2 / 3 workgroups (4 waves each): 32 ranks x 64 tokens x 7168 columns 108 / 112, 64 x 128 x
+// 7168 407 / 412, 16 x 128 x 2048 44.9 / 45.0. The layer variants also combine with them, and gathers want
+// more waves: at 3 / 4 workgroups 32 x 64 x 7168 168 / 158, 64 x 128 x 7168 636 / 629.
+// With one or two choices a wave has little to write: all that fit, and beyond one batch each the count
+// workgroups join when they have counted (top-1 of 1024 columns on 32 ranks, us per layer without and with:
+// 1024 tokens each, layout and dispatch 120 / 99; 256 tokens each, the sentinel layer 48.7 / 46.4).
+constexpr int kSendPerCu = 2, kSendPerCuLayer = 4;
 hipError_t plan_decomposed(const Geom& g, int H, int count_groups, int sync, DecomposedPlan* plan) {
-  const bool layer = sync != kDafNone;
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  const bool buf_x = g.T * (int64_t)H * 2 >= kBufferLoadXBytes;
-  const size_t lds = decomposed_lds_bytes(g);
-  if (e == hipSuccess)
-    e = buf_x ? occupancy_of<true>(sync, &per_cu, lds) : occupancy_of<false>(sync, &per_cu, lds);
+  if (e == hipSuccess) e = occupancy_of(sync, &per_cu, decomposed_lds_bytes(g));
   if (e != hipSuccess) return e;
   plan->capacity = per_cu * cus;
   // Default split: one count workgroup per layout chunk, at most a quarter of what the device
   // holds at once.
   int nc = count_groups > 0 ? count_groups : std::min(g.nblk, std::max(1, plan->capacity / 4));
   plan->count_groups = nc;
-  const int nv = H / 8;
-  const int chunks = (nv + kBf16Cols - 1) / kBf16Cols;
-  const int64_t unit_blocks = (g.T * chunks + kWavesPerBlock - 1) / kWavesPerBlock;
-  const int64_t room = plan->capacity - nc;
-  if (!layer) {
-    plan->send_groups = (int)std::max<int64_t>(1, std::min<int64_t>(room, unit_blocks));
-    plan->combine_groups = 0;
-  } else {
-    // The rest split evenly between send and combine workgroups, each no more than it has units for.
-    const int cchunks = (nv + kWave - 1) / kWave;
-    const int64_t combine_blocks = (g.T * cchunks + kWavesPerBlock - 1) / kWavesPerBlock;
-    plan->send_groups = (int)std::max<int64_t>(1, std::min<int64_t>(room / 2, unit_blocks));
-    plan->combine_groups = (int)std::max<int64_t>(1, std::min<int64_t>(room - plan->send_groups, combine_blocks));
-  }
-  plan->grid = nc + plan->send_groups + plan->combine_groups;
+  const int64_t cchunks = (H / 8 + kWave - 1) / kWave;
+  // Send: batches of up to four tokens, all workgroups with as many batches as the next.
+  const bool few = g.k <= kFewChoices;
+  const int most_per_cu = few ? 1 << 16 : sync == kDafNone ? kSendPerCu : kSendPerCuLayer;
+  const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(plan->capacity - nc, (int64_t)most_per_cu * cus));
+  const int64_t room = groups + (few && g.T > groups * kWavesPerBlock ? nc : 0);
+  const int64_t rounds = std::max<int64_t>(1, (g.T + room * kWavesPerBlock - 1) / (room * kWavesPerBlock));
+  const int64_t even = (g.T + room * rounds - 1) / (room * rounds);
+  // More tokens per batch than that where a row is so short that a wave would load fewer than kSendAhead
+  // units, and every wave should place a token, as long as each compute unit keeps a workgroup (128 tokens of
+  // 2048 columns: one per batch 26.6 us, four 46.1).
+  const int64_t full = (kSendAhead * kWavesPerBlock + cchunks - 1) / cchunks;
+  plan->batch = (int)std::min<int64_t>(kWavesPerBlock, std::max(even, std::min(full, g.T / cus)));
+  plan->batch = std::max(1, plan->batch);
+  plan->send_groups = (int)std::max<int64_t>(1, std::min<int64_t>(groups, (g.T + plan->batch - 1) / plan->batch));
+  plan->grid = nc + plan->send_groups;
+  plan->senders = room > groups ? plan->grid : plan->send_groups;
+  // Combine: as many chunks per task as leave every wave a task, in runs of even length.
+  const int64_t waves = (int64_t)plan->grid * kWavesPerBlock;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(cchunks, (g.T * cchunks + waves - 1) / waves));
+  const int64_t runs = (cchunks + want - 1) / want;
+  plan->combine_run = (int)((cchunks + runs - 1) / runs);
   return hipSuccess;
 }
 
@@ -568,23 +628,18 @@ hipError_t launch_decomposed(const Geom& g, const int32_t* idx, int32_t* ws, con
   A.recv = static_cast<u32x4*>(recv);
   A.nv = H / 8;
   A.pv = pitch / 8;
-  A.chunks = (A.nv + kBf16Cols - 1) / kBf16Cols;
   A.cchunks = (A.nv + kWave - 1) / kWave;
   A.cap = cap;
   A.nc = plan.count_groups;
-  A.ns = plan.send_groups;
-  A.nco = plan.combine_groups;
+  A.ns = plan.senders;
+  A.crun = plan.combine_run;
+  A.batch = plan.batch;
   A.sync = ws + wl.sync;
   A.status = wait_status;
   A.spin_ticks = opts.spin_ticks;
   A.ready_target = opts.ready_target;
   const size_t lds = decomposed_lds_bytes(g);
-  const bool buf_x = g.T * (int64_t)H * 2 >= kBufferLoadXBytes;
-  const dim3 grid(plan.grid), block(kLayoutThreads);
-  if (buf_x)
-    launch_variant<true>(sync, grid, block, lds, stream, A);
-  else
-    launch_variant<false>(sync, grid, block, lds, stream, A);
+  launch_variant(sync, dim3(plan.grid), dim3(kLayoutThreads), lds, stream, A);
   return hipGetLastError();
 }
 

@@ -36,7 +36,6 @@ namespace epl {
 // of 64K rows of 1024 138.7 / 143.3 / 136.3; top-2 of 32K rows of 7168 606 / 575 / 585, of 32K rows of
 // 512 55.1 / 57.2 / 55.5; top-4 of 16K rows of 4096 259 / 243 / 248.
 constexpr int plain_waves_per_simd(bool few) { return few ? 6 : 4; }
-constexpr int kFewChoices = 2;
 template <class AtFn>
 __device__ __forceinline__ void plain_units(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row,
                                             u32x4* __restrict__ recv, int64_t T, int k, int nv, int pv, int chunks,
@@ -47,7 +46,7 @@ __device__ __forceinline__ void plain_units(const u32x4* __restrict__ x, const i
   for (int64_t u = (int64_t)blockIdx.x * kPlainWaves + threadIdx.x / kWave; u < units; u += stride) {
     const int64_t g = u / chunks;
     const int c = (int)(u - g * chunks);
-    dispatch_bf16_unit<false, 1>(
+    dispatch_bf16_unit(
         x,
         [&] {
           const int row = lane < k ? pair_row[g * k + lane] : -1;

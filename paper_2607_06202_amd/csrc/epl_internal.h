@@ -306,16 +306,19 @@ struct DecomposedOpts {
 };
 // Workgroups of the launch by role, and the device's co-resident capacity for it.
 struct DecomposedPlan {
-  int grid, count_groups, send_groups, combine_groups, capacity;
+  int grid, count_groups, send_groups, capacity;
+  int senders;      // workgroups that send: send_groups, or the whole grid
+  int batch;        // tokens a send workgroup takes at a time
+  int combine_run;  // 1 KiB column chunks per combine task
 };
-// How the layer variants' combine workgroups learn that a row chunk has arrived (Data-as-Flag):
-// kDafNone is the launch without combine workgroups (layout and dispatch only).
+// How the layer variants' combine learns that a row chunk has arrived (Data-as-Flag):
+// kDafNone is the launch without a combine (layout and dispatch only).
 constexpr int kDafNone = 0;       // no combine role
 constexpr int kDafSentinel = 1;   // Sentinel Polling: every element compared with the reserved pattern
 constexpr int kDafFlag = 2;       // Token-Flag Fusion: an epoch flag per 1 KiB chunk, stored after the chunk
 constexpr int kDafChecksum = 3;   // Data-for-Checksum: a salted hash per 1 KiB chunk, checked against the data
 hipError_t plan_decomposed(const Geom& g, int H, int count_groups, int sync, DecomposedPlan* plan);
-// sync != kDafNone: the layer variant, whose combine workgroups gather the rows into out with the
+// sync != kDafNone: the layer variant, whose workgroups then gather the rows into out with the
 // weights topk_w as the send workgroups write them; marks and epoch serve kDafFlag and kDafChecksum.
 hipError_t launch_decomposed(const Geom& g, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
                              const void* x, void* recv, int H, int pitch, int64_t cap, const DecomposedOpts& opts,

@@ -14,13 +14,14 @@ constexpr int kWavesPerBlock = kDispatchThreads / kWave;
 // runs each, dispatch us with 128 / 256 / 512 threads: skewed fp8 202.3-203.2 / 205.3-205.4 / 228.6.
 constexpr int kPlainThreads = 128;     // the plain bf16 dispatch kernel
 constexpr int kPlainWaves = kPlainThreads / kWave;
+constexpr int kFewChoices = 2;         // up to this many choices a wave has little to write, and more waves are run
 constexpr int kFp8Threads = 128;       // the fp8 dispatch kernel
 constexpr int kFp8Waves = kFp8Threads / kWave;
-// bf16 work unit of the one-launch and scheduled kernels: one token's columns
-// [u*kBf16Cols, (u+1)*kBf16Cols) in 16-byte vectors. The plain kernel's units are one vector per lane.
+// bf16 work unit of the small and scheduled kernels: one token's columns
+// [u*kBf16Cols, (u+1)*kBf16Cols) in 16-byte vectors. The plain and the decomposed kernel's units are
+// one vector per lane.
 constexpr int kBf16VPL = 4;                     // vectors per lane in one unit
 constexpr int kBf16Cols = kWave * kBf16VPL;     // 256 vectors = 4 KiB of a row
-constexpr int64_t kBufferLoadXBytes = 200ll << 20;  // x at least this large: buffer loads (see dispatch_bf16_unit)
 
 // Store one 16-byte vector at vector index v of a row of nv vectors through a buffer resource
 // scoped to that row, with an explicit cache policy. The resource bounds (nv * 16 bytes) also
@@ -36,61 +37,23 @@ __device__ __forceinline__ void store_row_policy(u32x4 val, u32x4* row_base, int
   __builtin_amdgcn_raw_buffer_store_b128(val, rsrc, v * 16, 0, POLICY);
 }
 
-// bf16: unit = (token g, column chunk c of VPL vectors per lane). The wave loads its chunk of x[g] once and stores it
-// to the k destination rows, interleaving destinations per vector. x rows are nv vectors apart,
-// recv rows pv (the receive pitch in 16-byte vectors).
-//
-// BUF_X selects how x is read, both with the default cache policy: buffer loads through a
-// resource bounded to the row, or plain global loads. With 4 KiB units, dispatch alone, x rotated, global
-// against buffer loads: EP=32 prefill 3293 / 3252 us, EP=256 380.5 / 376.3, EP=64 decode 176.4 / 178.1. The
-// decomposed launch takes buffer loads for an x of 200 MB or more, between decode's 117 MB and the
-// others' 235 MB and 1.9 GB; with 1 KiB units the form makes no difference.
-// row_of() returns, in lane j < k, the packed row of pair j (-1 if invalid); it is called after the
-// loads of x are issued, so whatever it loads is in flight together with them. An inactive wave
-// loads and calls row_of() (which may hold a workgroup barrier) but stores nothing. check(buf, on)
-// sees the unit's loaded vectors (on[u]: vector u lies inside the row) before they are stored, and
-// after(buf, on, my_row) runs once they are issued (my_row: lane j's packed row, as above).
-struct NoCheck {
-  __device__ __forceinline__ void operator()(const u32x4*, const bool*) const {}
-};
-struct NoAfter {
-  __device__ __forceinline__ void operator()(const u32x4*, const bool*, int) const {}
-};
-template <bool BUF_X, int VPL = kBf16VPL, class RowFn, class CheckFn = NoCheck, class AfterFn = NoAfter>
+// bf16: unit = (token g, 1 KiB column chunk c), one vector per lane. The wave loads its chunk of x[g]
+// once and stores it to the k destination rows. x rows are nv vectors apart, recv rows pv (the
+// receive pitch in 16-byte vectors). row_of() returns, in lane j < k, the packed row of pair j (-1 if
+// invalid); it is called after the load of x is issued, so whatever it loads is in flight with it.
+template <class RowFn>
 __device__ __forceinline__ void dispatch_bf16_unit(const u32x4* __restrict__ x, RowFn row_of, u32x4* __restrict__ recv,
-                                                   int64_t g, int c, int k, int nv, int pv, int64_t cap, int lane,
-                                                   bool active = true, CheckFn check = CheckFn(),
-                                                   AfterFn after = AfterFn()) {
-  const u32x4* xr = x + g * nv;
-  const int v0 = c * (kWave * VPL) + lane;
-  // Loads are unconditional (index clamped into the row) so that all of them are in flight
-  // together; only the stores are guarded. Default cache policy: it measured faster than
-  // nontemporal loads here, though x is read once.
-  u32x4 buf[VPL];
-  if constexpr (BUF_X) {
-    const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4*>(xr), 0, nv * 16, kBufferRsrcWord3);
-#pragma unroll
-    for (int u = 0; u < VPL; ++u) buf[u] = __builtin_amdgcn_raw_buffer_load_b128(xs, min(v0 + u * kWave, nv - 1) * 16, 0, 0);
-  } else {
-#pragma unroll
-    for (int u = 0; u < VPL; ++u) buf[u] = xr[min(v0 + u * kWave, nv - 1)];
-  }
+                                                   int64_t g, int c, int k, int nv, int pv, int64_t cap, int lane) {
+  const int v = c * kWave + lane;
+  // The load is unconditional (index clamped into the row); only the stores are guarded. Default cache
+  // policy: it measured faster than nontemporal loads here, though x is read once.
+  const u32x4 buf = x[g * nv + min(v, nv - 1)];
   const int my_row = row_of();
-  if (!active) return;
-  bool on[VPL];
-#pragma unroll
-  for (int u = 0; u < VPL; ++u) on[u] = v0 + u * kWave < nv;
-  check(buf, on);
-#pragma unroll
-  for (int u = 0; u < VPL; ++u) {
-    const int v = v0 + u * kWave;
-    for (int j = 0; j < k; ++j) {
-      const int row = __builtin_amdgcn_readlane(my_row, j);
-      if (row < 0 || row >= cap) continue;
-      if (v < nv) store_row_policy<kCachePolicySc1>(buf[u], recv + (int64_t)row * pv, nv, v);
-    }
+  for (int j = 0; j < k; ++j) {
+    const int row = __builtin_amdgcn_readlane(my_row, j);
+    if (row < 0 || row >= cap) continue;
+    if (v < nv) store_row_policy<kCachePolicySc1>(buf, recv + (int64_t)row * pv, nv, v);
   }
-  after(buf, on, my_row);
 }
 
 // fp8: unit = (token g, pass p) covering elements [1024p, 1024p + 1024). Lane l quantises
