@@ -12,12 +12,6 @@ namespace {
 
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p % a) == 0; }
 
-int bits_for(int n) {  // bits needed to represent values 0..n-1
-  int b = 0;
-  while ((1 << b) < n) ++b;
-  return b;
-}
-
 // Common config checks; EPL_OK if the shape is one the library handles.
 epl_status check_config(const epl_config* cfg) {
   if (!cfg) return EPL_ERR_INVALID_ARG;
@@ -34,30 +28,8 @@ epl_status check_config(const epl_config* cfg) {
 // Elements from one receive (and expert-output) row to the next.
 int pitch_of(const epl_config* cfg) { return cfg->row_pitch ? cfg->row_pitch : cfg->hidden; }
 
-// Chunking of each source rank's tokens for the layout kernels: whole tokens, at most
-// kMaxChunkPairs pairs per workgroup.
 epl::Geom make_geom(const epl_config* cfg) {
-  epl::Geom g;
-  g.R = cfg->num_ranks;
-  g.E = cfg->num_experts;
-  g.El = g.E / g.R;
-  g.k = cfg->topk;
-  g.Tr = cfg->tokens_per_rank;
-  g.T = (int64_t)g.R * g.Tr;
-  // Aim for >= 256 workgroups (the chip has 256 CUs) and >= 64 pairs per workgroup, with at
-  // most kMaxChunkPairs pairs per chunk.
-  const int cap = epl::kMaxChunkPairs / g.k;  // k <= 32 so cap >= 32
-  const int64_t want = std::max<int64_t>((g.T + 255) / 256, (64 + g.k - 1) / g.k);
-  const int ct = (int)std::min<int64_t>(want, cap);
-  g.CT = g.Tr < 1 ? 1 : std::min(ct, g.Tr);
-  g.NC = g.Tr < 1 ? 1 : (g.Tr + g.CT - 1) / g.CT;
-  g.nblk = g.R * g.NC;
-  g.ebits = bits_for(g.E);
-  g.rbits = bits_for(g.R);
-  g.inv_k = 1.0f / (float)g.k;
-  g.inv_El = 1.0f / (float)g.El;
-  g.inv_R = 1.0f / (float)g.R;
-  return g;
+  return epl::make_geom(cfg->num_ranks, cfg->num_experts, cfg->topk, cfg->tokens_per_rank);
 }
 
 size_t workspace_bytes(const epl::Geom& g) { return epl::ws_layout(g).total * sizeof(int32_t); }

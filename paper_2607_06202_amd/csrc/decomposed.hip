@@ -247,7 +247,6 @@ __device__ __forceinline__ uint64_t epoch_salt(uint64_t epoch) { return mix64(ep
 // Measured against handing out batches of units from a launch-wide counter, with the count
 // workgroups joining once their counting was done: that was slower (decode 416.7 against
 // 396.8 us per layer, the Qwen3-30B shape 61.2 against 50.7 us), the counter's atomics serialising.
-constexpr int kSendAhead = 4;
 template <int SYNC>
 __device__ __forceinline__ bool send_role(const DecomposedArgs& A, int j, int32_t* lds, int32_t* flag) {
   const int lane = threadIdx.x % kWave;
@@ -484,6 +483,7 @@ template <int SYNC>
 __global__ void __launch_bounds__(kLayoutThreads) __attribute__((amdgpu_waves_per_eu(5)))
     decomposed_kernel(DecomposedArgs A) {
   static_assert(kDispatchThreads == kLayoutThreads, "both roles run in 256-thread workgroups");
+  static_assert(kWavesPerBlock == kSendBatch, "a send workgroup's waves place one token each");
   extern __shared__ int32_t lds[];
   __shared__ int32_t red[kLayoutWaves];
   __shared__ int32_t scratch[kLayoutWaves];
@@ -551,47 +551,13 @@ static hipError_t occupancy_of(int sync, int* per_cu, size_t lds) {
   }
 }
 
-// Send workgroups per compute unit. Scattered writes go faster from fewer waves: layout and dispatch, us
-// per layer at 2 / 3 workgroups (4 waves each): 32 ranks x 64 tokens x 7168 columns 108 / 112, 64 x 128 x
-// 7168 407 / 412, 16 x 128 x 2048 44.9 / 45.0. The layer variants also combine with them, and gathers want
-// more waves: at 3 / 4 workgroups 32 x 64 x 7168 168 / 158, 64 x 128 x 7168 636 / 629.
-// With one or two choices a wave has little to write: all that fit, and beyond one batch each the count
-// workgroups join when they have counted (top-1 of 1024 columns on 32 ranks, us per layer without and with:
-// 1024 tokens each, layout and dispatch 120 / 99; 256 tokens each, the sentinel layer 48.7 / 46.4).
-constexpr int kSendPerCu = 2, kSendPerCuLayer = 4;
 hipError_t plan_decomposed(const Geom& g, int H, int count_groups, int sync, DecomposedPlan* plan) {
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess) e = occupancy_of(sync, &per_cu, decomposed_lds_bytes(g));
   if (e != hipSuccess) return e;
-  plan->capacity = per_cu * cus;
-  // Default split: one count workgroup per layout chunk, at most a quarter of what the device
-  // holds at once.
-  int nc = count_groups > 0 ? count_groups : std::min(g.nblk, std::max(1, plan->capacity / 4));
-  plan->count_groups = nc;
-  const int64_t cchunks = (H / 8 + kWave - 1) / kWave;
-  // Send: batches of up to four tokens, all workgroups with as many batches as the next.
-  const bool few = g.k <= kFewChoices;
-  const int most_per_cu = few ? 1 << 16 : sync == kDafNone ? kSendPerCu : kSendPerCuLayer;
-  const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(plan->capacity - nc, (int64_t)most_per_cu * cus));
-  const int64_t room = groups + (few && g.T > groups * kWavesPerBlock ? nc : 0);
-  const int64_t rounds = std::max<int64_t>(1, (g.T + room * kWavesPerBlock - 1) / (room * kWavesPerBlock));
-  const int64_t even = (g.T + room * rounds - 1) / (room * rounds);
-  // More tokens per batch than that where a row is so short that a wave would load fewer than kSendAhead
-  // units, and every wave should place a token, as long as each compute unit keeps a workgroup (128 tokens of
-  // 2048 columns: one per batch 26.6 us, four 46.1).
-  const int64_t full = (kSendAhead * kWavesPerBlock + cchunks - 1) / cchunks;
-  plan->batch = (int)std::min<int64_t>(kWavesPerBlock, std::max(even, std::min(full, g.T / cus)));
-  plan->batch = std::max(1, plan->batch);
-  plan->send_groups = (int)std::max<int64_t>(1, std::min<int64_t>(groups, (g.T + plan->batch - 1) / plan->batch));
-  plan->grid = nc + plan->send_groups;
-  plan->senders = room > groups ? plan->grid : plan->send_groups;
-  // Combine: as many chunks per task as leave every wave a task, in runs of even length.
-  const int64_t waves = (int64_t)plan->grid * kWavesPerBlock;
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(cchunks, (g.T * cchunks + waves - 1) / waves));
-  const int64_t runs = (cchunks + want - 1) / want;
-  plan->combine_run = (int)((cchunks + runs - 1) / runs);
+  *plan = split_decomposed(g, H, count_groups, sync, per_cu * cus, cus);
   return hipSuccess;
 }
 

@@ -8,15 +8,10 @@
 #include <stdint.h>
 
 #include "epl.h"
+#include "geometry.h"
 
 namespace epl {
 
-constexpr int kWave = 64;
-constexpr int kLayoutThreads = 256;
-constexpr int kLayoutWaves = kLayoutThreads / kWave;
-// Pairs handled by one layout workgroup ("chunk"); a chunk never spans two source ranks and
-// always holds whole tokens.
-constexpr int kMaxChunkPairs = 1024;
 constexpr int kLayoutSlots = EPL_MAX_EXPERTS / kLayoutThreads;  // per-lane slots covering E or R experts/ranks
 // The one-launch layout (small.hip) counts all T*k ids in every workgroup and deduplicates each source
 // rank's earlier tokens again, so it is used only up to these sizes; larger layouts take three
@@ -38,18 +33,6 @@ constexpr int kBufferRsrcWord3 = 0x00020000;
 // Cache-policy operand of the raw buffer builtins: bit 0 = sc0, bit 1 = nt, bit 4 = sc1.
 constexpr int kCachePolicySc1 = 16;
 constexpr int kCachePolicySc1Nt = 18;
-
-// Shape of one layout problem, derived on the host from epl_config.
-struct Geom {
-  int R, E, El, k, Tr;
-  int CT;     // tokens per chunk
-  int NC;     // chunks per source rank (>= 1)
-  int nblk;   // R * NC layout workgroups
-  int ebits;  // bits needed for an expert id (ballot-match key width)
-  int rbits;  // bits needed for a rank id
-  float inv_k, inv_El, inv_R;  // 1/k, 1/El, 1/R for exact small quotients
-  int64_t T;
-};
 
 // Workspace carve-up, in int32 elements.
 struct WsLayout {
@@ -304,19 +287,6 @@ struct DecomposedOpts {
   int64_t spin_ticks;
   int ready_target;
 };
-// Workgroups of the launch by role, and the device's co-resident capacity for it.
-struct DecomposedPlan {
-  int grid, count_groups, send_groups, capacity;
-  int senders;      // workgroups that send: send_groups, or the whole grid
-  int batch;        // tokens a send workgroup takes at a time
-  int combine_run;  // 1 KiB column chunks per combine task
-};
-// How the layer variants' combine learns that a row chunk has arrived (Data-as-Flag):
-// kDafNone is the launch without a combine (layout and dispatch only).
-constexpr int kDafNone = 0;       // no combine role
-constexpr int kDafSentinel = 1;   // Sentinel Polling: every element compared with the reserved pattern
-constexpr int kDafFlag = 2;       // Token-Flag Fusion: an epoch flag per 1 KiB chunk, stored after the chunk
-constexpr int kDafChecksum = 3;   // Data-for-Checksum: a salted hash per 1 KiB chunk, checked against the data
 hipError_t plan_decomposed(const Geom& g, int H, int count_groups, int sync, DecomposedPlan* plan);
 // sync != kDafNone: the layer variant, whose workgroups then gather the rows into out with the
 // weights topk_w as the send workgroups write them; marks and epoch serve kDafFlag and kDafChecksum.

@@ -1,0 +1,130 @@
+// Host-side geometry of the launches: how a layout is cut into chunks, which kernels a layer takes and
+// how large their grids are. Plain C++ on integers, without HIP, so that it is checked on the host over
+// all shapes.
+#pragma once
+
+#include <algorithm>
+#include <limits.h>
+#include <stddef.h>
+#include <stdint.h>
+
+#include "epl.h"
+
+namespace epl {
+
+constexpr int kWave = 64;
+constexpr int kLayoutThreads = 256;
+constexpr int kLayoutWaves = kLayoutThreads / kWave;
+// Pairs handled by one layout workgroup ("chunk"); a chunk never spans two source ranks and
+// always holds whole tokens.
+constexpr int kMaxChunkPairs = 1024;
+
+// Shape of one layout problem, derived on the host from epl_config.
+struct Geom {
+  int R, E, El, k, Tr;
+  int CT;     // tokens per chunk
+  int NC;     // chunks per source rank (>= 1)
+  int nblk;   // R * NC layout workgroups
+  int ebits;  // bits needed for an expert id (ballot-match key width)
+  int rbits;  // bits needed for a rank id
+  float inv_k, inv_El, inv_R;  // 1/k, 1/El, 1/R for exact small quotients
+  int64_t T;
+};
+
+inline int bits_for(int n) {  // bits needed to represent values 0..n-1
+  int b = 0;
+  while ((1 << b) < n) ++b;
+  return b;
+}
+
+// Chunking of each source rank's tokens for the layout kernels: whole tokens, at most
+// kMaxChunkPairs pairs per workgroup.
+inline Geom make_geom(int R, int E, int k, int Tr) {
+  Geom g;
+  g.R = R;
+  g.E = E;
+  g.El = g.E / g.R;
+  g.k = k;
+  g.Tr = Tr;
+  g.T = (int64_t)g.R * g.Tr;
+  // Aim for >= 256 workgroups (the chip has 256 CUs) and >= 64 pairs per workgroup, with at
+  // most kMaxChunkPairs pairs per chunk.
+  const int cap = kMaxChunkPairs / g.k;  // k <= 32 so cap >= 32
+  const int64_t want = std::max<int64_t>((g.T + 255) / 256, (64 + g.k - 1) / g.k);
+  const int ct = (int)std::min<int64_t>(want, cap);
+  g.CT = g.Tr < 1 ? 1 : std::min(ct, g.Tr);
+  g.NC = g.Tr < 1 ? 1 : (g.Tr + g.CT - 1) / g.CT;
+  g.nblk = g.R * g.NC;
+  g.ebits = bits_for(g.E);
+  g.rbits = bits_for(g.R);
+  g.inv_k = 1.0f / (float)g.k;
+  g.inv_El = 1.0f / (float)g.El;
+  g.inv_R = 1.0f / (float)g.R;
+  return g;
+}
+
+// ------------------------------------------------------------------------ one-launch layers
+constexpr int kFewChoices = 2;    // up to this many choices a wave has little to write, and more waves are run
+constexpr int kSendBatch = 4;     // most tokens a send workgroup takes at a time: one per wave
+constexpr int kSendAhead = 4;     // 1 KiB units a send wave loads together (measured beside send_role)
+
+// How the layer variants' combine learns that a row chunk has arrived (Data-as-Flag):
+// kDafNone is the launch without a combine (layout and dispatch only).
+constexpr int kDafNone = 0;       // no combine role
+constexpr int kDafSentinel = 1;   // Sentinel Polling: every element compared with the reserved pattern
+constexpr int kDafFlag = 2;       // Token-Flag Fusion: an epoch flag per 1 KiB chunk, stored after the chunk
+constexpr int kDafChecksum = 3;   // Data-for-Checksum: a salted hash per 1 KiB chunk, checked against the data
+
+// Workgroups of the launch by role, and the device's co-resident capacity for it.
+struct DecomposedPlan {
+  int grid, count_groups, send_groups, capacity;
+  int senders;      // workgroups that send: send_groups, or the whole grid
+  int batch;        // tokens a send workgroup takes at a time
+  int combine_run;  // 1 KiB column chunks per combine task
+};
+
+// Send workgroups per compute unit. Scattered writes go faster from fewer waves: layout and dispatch, us
+// per layer at 2 / 3 workgroups (4 waves each): 32 ranks x 64 tokens x 7168 columns 108 / 112, 64 x 128 x
+// 7168 407 / 412, 16 x 128 x 2048 44.9 / 45.0. The layer variants also combine with them, and gathers want
+// more waves: at 3 / 4 workgroups 32 x 64 x 7168 168 / 158, 64 x 128 x 7168 636 / 629.
+// With one or two choices a wave has little to write: all that fit, and beyond one batch each the count
+// workgroups join when they have counted (top-1 of 1024 columns on 32 ranks, us per layer without and with:
+// 1024 tokens each, layout and dispatch 120 / 99; 256 tokens each, the sentinel layer 48.7 / 46.4).
+constexpr int kSendPerCu = 2, kSendPerCuLayer = 4;
+
+// The plan on a device of `cus` compute units that holds `capacity` workgroups of the kernel at once. A
+// grid beyond the capacity (a count_groups that leaves no room for send workgroups) is the caller's to
+// refuse; sums that would not fit an int saturate, so that such a grid is never below the capacity.
+inline DecomposedPlan split_decomposed(const Geom& g, int H, int count_groups, int sync, int capacity, int cus) {
+  DecomposedPlan plan;
+  plan.capacity = capacity;
+  // Default split: one count workgroup per layout chunk, at most a quarter of what the device
+  // holds at once.
+  const int64_t nc = count_groups > 0 ? count_groups : std::min(g.nblk, std::max(1, capacity / 4));
+  plan.count_groups = (int)nc;
+  const int64_t cchunks = (H / 8 + kWave - 1) / kWave;
+  // Send: batches of up to four tokens, all workgroups with as many batches as the next.
+  const bool few = g.k <= kFewChoices;
+  const int most_per_cu = few ? 1 << 16 : sync == kDafNone ? kSendPerCu : kSendPerCuLayer;
+  const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(capacity - nc, (int64_t)most_per_cu * cus));
+  const int64_t room = groups + (few && g.T > groups * kSendBatch ? nc : 0);
+  const int64_t rounds = std::max<int64_t>(1, (g.T + room * kSendBatch - 1) / (room * kSendBatch));
+  const int64_t even = (g.T + room * rounds - 1) / (room * rounds);
+  // More tokens per batch than that where a row is so short that a wave would load fewer than kSendAhead
+  // units, and every wave should place a token, as long as each compute unit keeps a workgroup (128 tokens of
+  // 2048 columns: one per batch 26.6 us, four 46.1).
+  const int64_t full = (kSendAhead * kSendBatch + cchunks - 1) / cchunks;
+  const int64_t batch = std::min<int64_t>(kSendBatch, std::max(even, std::min(full, g.T / cus)));
+  plan.batch = (int)std::max<int64_t>(1, batch);
+  plan.send_groups = (int)std::max<int64_t>(1, std::min<int64_t>(groups, (g.T + plan.batch - 1) / plan.batch));
+  plan.grid = (int)std::min<int64_t>(nc + plan.send_groups, INT_MAX);
+  plan.senders = room > groups ? plan.grid : plan.send_groups;
+  // Combine: as many chunks per task as leave every wave a task, in runs of even length.
+  const int64_t waves = (int64_t)plan.grid * kLayoutWaves;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(cchunks, (g.T * cchunks + waves - 1) / waves));
+  const int64_t runs = (cchunks + want - 1) / want;
+  plan.combine_run = (int)((cchunks + runs - 1) / runs);
+  return plan;
+}
+
+}  // namespace epl

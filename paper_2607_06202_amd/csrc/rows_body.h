@@ -14,7 +14,6 @@ constexpr int kWavesPerBlock = kDispatchThreads / kWave;
 // runs each, dispatch us with 128 / 256 / 512 threads: skewed fp8 202.3-203.2 / 205.3-205.4 / 228.6.
 constexpr int kPlainThreads = 128;     // the plain bf16 dispatch kernel
 constexpr int kPlainWaves = kPlainThreads / kWave;
-constexpr int kFewChoices = 2;         // up to this many choices a wave has little to write, and more waves are run
 constexpr int kFp8Threads = 128;       // the fp8 dispatch kernel
 constexpr int kFp8Waves = kFp8Threads / kWave;
 // bf16 work unit of the small and scheduled kernels: one token's columns
