@@ -137,8 +137,7 @@ template <int VPL>
 void launch_combine_vpl(const u32x4* y, const float* w, const int32_t* pair_row, u32x4* out, int64_t T, int k, int nv,
                         int pv, hipStream_t stream) {
   const int chunks = (nv + combine_cols<VPL>() - 1) / combine_cols<VPL>();
-  const int64_t blocks = (T * chunks + kCombineWaves - 1) / kCombineWaves;
-  const dim3 grid((unsigned)std::min<int64_t>(blocks, 1 << 30));
+  const dim3 grid(unit_grid(T * chunks, kCombineWaves, kCombineThreads));
   if (k <= kGather)
     hipLaunchKernelGGL((combine_kernel<true, VPL>), grid, dim3(kCombineThreads), 0, stream, y, w, pair_row, out, T, k,
                        nv, pv, chunks);

@@ -113,7 +113,7 @@ hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* re
   const int nv = H / 8;
   const int chunks = (nv + kWave - 1) / kWave;
   const int64_t units = T * chunks;
-  const dim3 grid((unsigned)std::min<int64_t>((units + kPlainWaves - 1) / kPlainWaves, 1 << 30));
+  const dim3 grid(unit_grid(units, kPlainWaves, kPlainThreads));
   const u32x4* xv = static_cast<const u32x4*>(x);
   u32x4* rv = static_cast<u32x4*>(recv);
   if (k <= kFewChoices)
@@ -132,7 +132,7 @@ hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* r
   const int nv = H / 8;
   const int chunks = (nv + kWave - 1) / kWave;
   const int64_t units = T * chunks;
-  const dim3 grid((unsigned)std::min<int64_t>((units + kPlainWaves - 1) / kPlainWaves, 1 << 30));
+  const dim3 grid(unit_grid(units, kPlainWaves, kPlainThreads));
   const u32x4* xv = static_cast<const u32x4*>(x);
   u32x4* rv = static_cast<u32x4*>(recv);
   if (k <= kFewChoices)
@@ -153,7 +153,7 @@ hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* rec
   if (T == 0) return hipSuccess;
   const int npass = (H + 1023) / 1024;
   const int64_t units = T * npass;
-  const dim3 grid((unsigned)std::min<int64_t>((units + kFp8Waves - 1) / kFp8Waves, 1 << 30));
+  const dim3 grid(unit_grid(units, kFp8Waves, kFp8Threads));
   hipLaunchKernelGGL(dispatch_fp8_kernel, grid, dim3(kFp8Threads), 0, stream, static_cast<const u32x4*>(x),
                      pair_row, static_cast<u32x4*>(recv), recv_scale, T, k, H, pitch / 16, npass, cap);
   return hipGetLastError();

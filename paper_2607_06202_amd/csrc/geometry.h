@@ -63,6 +63,14 @@ inline Geom make_geom(int R, int E, int k, int Tr) {
   return g;
 }
 
+// ------------------------------------------------------------------------ row kernels
+// Workgroups for `units` units, `per_group` to a workgroup of `threads` threads, of a kernel that strides
+// over its units. HIP takes fewer than 2^32 threads per grid dimension (gridDim * blockDim), which 1 KiB
+// units of a 64 GiB x would pass.
+inline unsigned unit_grid(int64_t units, int per_group, int threads) {
+  return (unsigned)std::min<int64_t>((units + per_group - 1) / per_group, UINT32_MAX / threads);
+}
+
 // ------------------------------------------------------------------------ one-launch layers
 constexpr int kFewChoices = 2;    // up to this many choices a wave has little to write, and more waves are run
 constexpr int kSendBatch = 4;     // most tokens a send workgroup takes at a time: one per wave

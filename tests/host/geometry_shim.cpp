@@ -10,4 +10,6 @@ void plan_decomposed(int R, int E, int k, int Tr, int H, int count_groups, int s
   for (int i = 0; i < 6; ++i) out[i] = v[i];
 }
 
+unsigned unit_grid(int64_t units, int per_group, int threads) { return epl::unit_grid(units, per_group, threads); }
+
 }  // extern "C"

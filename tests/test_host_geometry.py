@@ -31,3 +31,20 @@ def test_count_groups_beyond_the_device_give_a_grid_beyond_it(geo, sync, k, coun
     once: the caller compares grid with capacity, so the grid's sum must not wrap below it."""
     p = plan(geo, 64, 256, k, 128, 7168, count_groups, sync)
     assert p["count_groups"] == count_groups and p["grid"] > 1280
+
+
+@pytest.mark.parametrize("T,pieces", [
+    (8 * 4194304, 2),              # 32M tokens of 520 columns: 2^32 threads at two waves per workgroup
+    (4793491, 14),                 # 64 GiB of 7168-column tokens
+    ((1 << 31) - 2, 1), ((1 << 31) - 2, 2048),
+    (1, 1), (3, 1), (8192, 14)])
+@pytest.mark.parametrize("per_group,threads", [(2, 128), (4, 256)])
+def test_row_kernel_grids_stay_below_the_launch_limit(geo, T, pieces, per_group, threads):
+    """gridDim * blockDim < 2^32, every unit within a strided grid's reach, and one workgroup per
+    per_group units wherever that many fit."""
+    geo.unit_grid.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    geo.unit_grid.restype = ctypes.c_uint
+    n = geo.unit_grid(T * pieces, per_group, threads)
+    want = -(-T * pieces // per_group)
+    assert 1 <= n and n * threads < 1 << 32
+    assert n == want or (n < want and (n + 1) * threads >= 1 << 32)
