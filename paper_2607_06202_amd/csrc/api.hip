@@ -88,7 +88,8 @@ epl_status check_layout_dispatch(const epl_config* cfg, const int32_t* topk_idx,
 }
 
 bool rows_fused(const epl::Geom& g, const epl_config* cfg) {
-  return !epl::layout_single(g) && epl::fused_dispatch_ok(g, cfg->payload == EPL_PAYLOAD_FP8_E4M3);
+  return !epl::layout_single(g) && epl::fused_dispatch_ok(g, cfg->payload == EPL_PAYLOAD_FP8_E4M3) &&
+         epl::place_layout(g);
 }
 
 // The layout: histogram and place for the fused geometries, whose row kernel writes recv_src and recv_j,

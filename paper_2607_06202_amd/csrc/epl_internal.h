@@ -248,10 +248,8 @@ hipError_t launch_layout_counts(const Geom& g, const int32_t* idx, int32_t* ws, 
 hipError_t launch_layout_finalize(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* expert_off,
                                   int32_t* rank_off, int32_t* seg_off, int32_t* pair_row, int32_t* pair_rslot,
                                   int32_t* recv_src, int32_t* recv_j, hipStream_t stream);
-// Layouts whose [nblk][E] count matrix every workgroup can sum for itself: the whole layout in two launches
-// (count and place), recv_src and recv_j only with write_src.
-constexpr int kPlaceMaxChunks = 512;
-bool place_layout(const Geom& g);
+// The geometries place_layout accepts: the whole layout in two launches (count and place), recv_src and
+// recv_j only with write_src.
 hipError_t launch_layout_place(const Geom& g, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
                                bool write_src, hipStream_t stream);
 hipError_t launch_layout(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* send_cnt, int32_t* rank_cnt,

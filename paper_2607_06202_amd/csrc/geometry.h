@@ -63,6 +63,45 @@ inline Geom make_geom(int R, int E, int k, int Tr) {
   return g;
 }
 
+// ------------------------------------------------------------------------ layouts in two launches
+// route_count and route_place (layout.hip), for layouts of few chunks.
+constexpr int kPlaceMaxChunks = 512;
+constexpr int kPlaceLanes = 32;    // threads that read one row of counts, 16 bytes (eight experts) each
+constexpr int kPlaceRows = kLayoutThreads / kPlaceLanes;  // rows read side by side
+constexpr int kPlaceExperts = 8 * kPlaceLanes;
+constexpr int kPlaceAhead = 8;     // group rows in flight per thread
+constexpr int kGroupChunks = 4;    // chunks whose counts route_count also sums
+
+// The chunks that are launched. A few chunks past 256 (where the source ranks do not divide it) would
+// make every workgroup wait for a second batch of group rows: 264 chunks took 8.1 us, 256 6.5. Slightly
+// longer chunks avoid it, so there are never more of them than in g (the workspace is sized for g).
+inline Geom place_geom(const Geom& geom) {
+  Geom g = geom;
+  constexpr int kOneBatch = kPlaceAhead * kPlaceRows * kGroupChunks;
+  if (g.nblk > kOneBatch && g.R <= kOneBatch) {
+    const int per_rank = kOneBatch / g.R;
+    g.CT = std::min((g.Tr + per_rank - 1) / per_rank, kMaxChunkPairs / g.k);
+    g.NC = (g.Tr + g.CT - 1) / g.CT;
+    g.nblk = g.R * g.NC;
+  }
+  return g;
+}
+
+// Bound on the pairs of the group rows that one thread of route_place adds up. Every run of NC chunks
+// holds one rank's tokens, so a group of kGroupChunks holds as many whole ranks' as fit, and at most CT
+// tokens in each chunk that is left.
+inline int64_t place_sum(const Geom& launched) {
+  const Geom& g = launched;
+  const int64_t rows = (g.nblk + kGroupChunks * kPlaceRows - 1) / (kGroupChunks * kPlaceRows);
+  const int64_t tokens = (int64_t)(kGroupChunks / g.NC) * g.Tr + (int64_t)(kGroupChunks % g.NC) * g.CT;
+  return rows * tokens * g.k;
+}
+
+// Layouts whose count matrix every workgroup of route_place can sum for itself, in 16-bit halves.
+inline bool place_layout(const Geom& g) {
+  return g.E <= kPlaceExperts && g.nblk <= kPlaceMaxChunks && place_sum(place_geom(g)) < 65536;
+}
+
 // ------------------------------------------------------------------------ row kernels
 // Workgroups for `units` units, `per_group` to a workgroup of `threads` threads, of a kernel that strides
 // over its units. HIP takes fewer than 2^32 threads per grid dimension (gridDim * blockDim), which 1 KiB

@@ -156,11 +156,6 @@ __global__ void __launch_bounds__(kLayoutThreads)
 // workgroup has four waves: sixteen, with a quarter of the loads each, took longer to start, to meet and
 // to add up (8.2 us at 256 chunks).
 constexpr int kCountThreads = 1024;
-constexpr int kPlaceLanes = 32;    // threads that read one row of counts, 16 bytes (eight experts) each
-constexpr int kPlaceRows = kLayoutThreads / kPlaceLanes;  // rows read side by side
-constexpr int kPlaceExperts = 8 * kPlaceLanes;
-constexpr int kPlaceAhead = 8;     // group rows in flight per thread
-constexpr int kGroupChunks = 4;
 constexpr int kGroupWaves = kCountThreads / kWave / kGroupChunks;  // waves of route_count per chunk
 
 // One workgroup per kGroupChunks chunks, four waves each: the chunks' rows of cnt and the group's row of
@@ -365,24 +360,11 @@ static size_t finalize_lds_bytes(const Geom& g) {
   return sizeof(int32_t) * ((size_t)(g.E + 1) + g.E + g.R + (size_t)kLayoutWaves * (g.E + g.R));
 }
 
-bool place_layout(const Geom& g) {
-  // A thread's sums of group rows fit in 16 bits.
-  const int64_t rows = (g.nblk + kGroupChunks * kPlaceRows - 1) / (kGroupChunks * kPlaceRows);
-  return g.E <= kPlaceExperts && g.nblk <= kPlaceMaxChunks && rows * kGroupChunks * g.CT * g.k < 65536;
-}
-
 hipError_t launch_layout_place(const Geom& geom, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
                                bool write_src, hipStream_t stream) {
+  if (!place_layout(geom)) return hipErrorInvalidValue;  // its callers ask first
   const WsLayout wl = ws_layout(geom);
-  Geom g = geom;
-  // A few chunks past 256 (where the source ranks do not divide it) would make every workgroup wait for a
-  // second batch of group rows: 264 chunks took 8.1 us, 256 6.5. Slightly longer chunks avoid it.
-  constexpr int kOneBatch = kPlaceAhead * kPlaceRows * kGroupChunks;
-  if (g.nblk > kOneBatch) {
-    g.CT = std::min((g.Tr + kOneBatch / g.R - 1) / (kOneBatch / g.R), kMaxChunkPairs / g.k);
-    g.NC = (g.Tr + g.CT - 1) / g.CT;
-    g.nblk = g.R * g.NC;
-  }
+  const Geom g = place_geom(geom);
   int32_t* cnt = ws + wl.cnt;
   int32_t* group_cnt = ws + wl.chunk_e;
   int32_t* chunk_r = ws + wl.chunk_r;

@@ -1,10 +1,11 @@
-"""epl_layout_dispatch in three launches (counts, placement, rows; layouts of more than 16384 pairs, at
-most 512 chunks and 256 experts) against the CPU oracle, bit for bit, at the edges of its count
-matrix: odd and small numbers of experts (rows of counts that end inside a 16-byte load), a last group of
-fewer than four chunks, source ranks whose first chunk lies inside a group, more than 256 chunks, a
-single source rank, 200 and more chunks per rank, chunks of more than 256 pairs (more steps per wave),
-k that does not divide 64, every pair on one expert (the largest 16-bit sums), one more chunk-pair than
-the 16-bit bound allows (the general path), ids 4 bytes past 16-byte alignment; fp8 rows."""
+"""epl_layout_dispatch in three launches (counts, placement, rows: layouts of more than 16384 pairs, of at
+most 512 chunks and 256 experts, whose 16-bit sums fit) against the CPU oracle, bit for bit, at the edges of its
+count matrix: odd and small numbers of experts (rows of counts that end inside a 16-byte load), a last group of
+fewer than four chunks, source ranks whose first chunk lies inside a group, layouts whose chunks are made longer
+so that at most 256 of them are launched, a second batch of group rows (more than 256 chunks launched), a single
+source rank, chunks of more than 256 pairs (more steps per wave), k that does not divide 64, every pair on one
+expert up to the largest 16-bit sums (61440) and one token more (the general path), ids 4 bytes past 16-byte
+alignment; fp8 rows."""
 import numpy as np
 import pytest
 import torch
@@ -20,13 +21,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("R,E,k,Tr,payload,routing", [
     (1, 7, 3, 6000, "bf16", "any"),       # one rank, odd E: a row of counts is one short load
     (3, 255, 5, 1111, "bf16", "any"),     # odd E, ragged chunks, ranks starting inside a group
-    (24, 192, 8, 128, "bf16", "any"),     # 264 chunks: longer ones are taken
+    (24, 192, 8, 128, "bf16", "any"),     # 264 chunks: 240 longer ones are taken
     (130, 130, 8, 16, "bf16", "any"),     # one chunk per rank, a last group of two
     (16, 256, 22, 100, "bf16", "any"),    # k that does not divide 64
     (8, 64, 1, 3000, "bf16", "any"),      # top-1
     (2, 16, 8, 8192, "bf16", "one"),      # all pairs on one expert, 512 pairs per chunk
-    (1, 256, 8, 32640, "bf16", "one"),    # 1020 pairs per chunk, all on one expert
+    (1, 256, 8, 32640, "bf16", "one"),    # 255 chunks of 1024 pairs, all on one expert
     (64, 256, 8, 512, "bf16", "any"),     # 256 chunks of 1024 pairs
+    (1, 256, 8, 40000, "bf16", "any"),    # 313 chunks of 1024 pairs: a second batch, partly filled
+    (1, 256, 8, 61440, "bf16", "one"),    # 480 chunks of 1024 pairs on one expert: sums of 61440
+    (1, 256, 8, 61441, "bf16", "one"),    # 481 chunks: the general path
+    (241, 241, 8, 130, "bf16", "any"),    # two chunks per rank, of 128 and 2 tokens
+    (249, 249, 8, 193, "fp8", "one"),     # 498 chunks, of 128 and 65 tokens by turns, all on one expert
     (300, 300, 4, 20, "bf16", "any"),     # more than 256 experts: the general path
     (5, 40, 7, 700, "fp8", "any"),
     (256, 256, 8, 40, "fp8", "any"),

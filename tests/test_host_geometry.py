@@ -48,3 +48,50 @@ def test_row_kernel_grids_stay_below_the_launch_limit(geo, T, pieces, per_group,
     want = -(-T * pieces // per_group)
     assert 1 <= n and n * threads < 1 << 32
     assert n == want or (n < want and (n + 1) * threads >= 1 << 32)
+
+
+def chunks(geo, R, E, k, Tr):
+    out = (ctypes.c_int * 8)()
+    geo.layout_chunks(R, E, k, Tr, out)
+    return dict(zip(("CT", "NC", "nblk", "pCT", "pNC", "pnblk", "sum", "place"), out))
+
+
+def place_shapes():
+    """Ranks of up to 256 x choices x tokens per rank around every place where the chunks change: one
+    chunk and the longest chunks per rank, 256 and 512 chunks, powers of two and their neighbours."""
+    for R in sorted({1, 2, 3, 5, 7, 8, 16, 24, 31, 32, 43, 64, 85, 86, 100, 127, 128, 129, 130, 170, 171, 172, 200, 240,
+                     241, 250, 255, 256}):
+        for k in (1, 2, 3, 5, 7, 8, 9, 13, 16, 22, 23, 31, 32):
+            cap = 1024 // k
+            around = [cap, 2 * cap, 3 * cap, 256 * cap // R, 512 * cap // R, 256 // R + 1, 61440 // R, 16384 // R]
+            around += [1 << i for i in range(17)]
+            for Tr in sorted({t + d for t in around for d in (-1, 0, 1)}):
+                if 0 <= Tr * R * k < 1 << 31:
+                    yield R, R * (256 // R), k, Tr
+
+
+def test_place_kernel_chunks(geo):
+    """route_place over all shapes: the chunks that are launched cover every rank's tokens, are no more than
+    the workspace is sized for and fit the kernel's steps; the bound on its 16-bit sums holds for the sums
+    counted chunk by chunk, and no layout is taken whose sums can reach 2^16. The bf16 layouts of at most 256
+    pairs per chunk, whose row kernel writes recv_src and recv_j, are all taken."""
+    taken = 0
+    for R, E, k, Tr in place_shapes():
+        g = chunks(geo, R, E, k, Tr)
+        what = (R, E, k, Tr, g)
+        assert g["pnblk"] <= g["nblk"] and g["pnblk"] == R * g["pNC"], what
+        assert g["pCT"] * g["pNC"] >= Tr and g["pCT"] * k <= 1024, what
+        counted = geo.place_sum_counted(R, E, k, Tr)
+        assert counted <= g["sum"], what
+        if g["place"]:
+            taken += 1
+            assert counted < 65536 and g["nblk"] <= 512, what
+            share, tpw = -(-min(g["pCT"], max(Tr, 1)) // 4), 64 // k  # tokens per wave, and per step
+            assert -(-share // tpw) <= (2 if g["pCT"] * k <= 256 else 6), what
+        if g["CT"] * k <= 256:
+            assert g["place"], what
+    assert taken > 1000
+    assert not chunks(geo, 257, 257, 8, 100)["place"]   # more than 256 experts
+    assert chunks(geo, 1, 256, 8, 61440) == dict(CT=128, NC=480, nblk=480, pCT=128, pNC=480, pnblk=480, sum=61440, place=1)
+    assert not chunks(geo, 1, 256, 8, 61441)["place"]   # 481 chunks: sums of up to 65536
+    assert chunks(geo, 241, 241, 8, 130)["place"]       # longer chunks than the layout's own
