@@ -116,12 +116,11 @@ hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const epl_layout_
 hipError_t run_layout_dispatch(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx,
                                const epl_layout_buffers* L, int32_t* ws, const void* x, void* recv, float* recv_scale,
                                int64_t cap, hipStream_t s) {
-  if (epl::small_layout(g))
-    return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap,
-                                             cfg->payload == EPL_PAYLOAD_FP8_E4M3, s);
   const bool fp8 = cfg->payload == EPL_PAYLOAD_FP8_E4M3;
+  if (epl::small_dispatch(g, cfg->hidden, fp8))
+    return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap, fp8, s);
   hipError_t e;
-  if (!epl::place_layout(g)) {
+  if (epl::small_layout(g) || !epl::place_layout(g)) {
     if ((e = run_counts(g, cfg, topk_idx, L, ws, s)) != hipSuccess) return e;
     return run_rows(g, cfg, L, x, recv, recv_scale, cap, s);
   }

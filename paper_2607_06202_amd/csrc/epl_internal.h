@@ -13,19 +13,6 @@
 namespace epl {
 
 constexpr int kLayoutSlots = EPL_MAX_EXPERTS / kLayoutThreads;  // per-lane slots covering E or R experts/ranks
-// The one-launch layout (small.hip) counts all T*k ids in every workgroup and deduplicates each source
-// rank's earlier tokens again, so it is used only up to these sizes; larger layouts take three
-// launches. Whole layer of 2048 columns, layout and dispatch in one launch against three: 16K pairs
-// on 32 ranks 35.9 / 39.2 us, 24K 56.2 / 55.2, 32K 71.6 / 69.2. The rank limit keeps the second pass
-// short: 16K pairs on one rank took 39.7 / 37.5 us, 16K of top-1 67.6 / 44.2, 12K on two ranks
-// 29.2 / 32.1.
-constexpr int64_t kSingleMaxPairs = 16384;     // T*k
-constexpr int64_t kSingleMaxRankPairs = 4096;  // Tr*k
-// Bound on 9 E + 6 R for epl_layout alone, whose launch count (epl_layout_launches) it is part of.
-// epl_layout_dispatch has no such bound: 4K pairs on 1024 ranks of one expert take 26.6 us per layer in
-// one launch, 51.9 in three.
-constexpr int64_t kSingleMaxTable = 12287;
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Buffer resource descriptor word 3 for raw (untyped) buffer accesses on CDNA3/CDNA4.
@@ -239,8 +226,6 @@ __device__ __forceinline__ void st32(T* p, T v) {
 }
 
 // ---------------------------------------------------------------- launchers (host side)
-bool small_layout(const Geom& g);   // true if epl_layout_dispatch runs as one launch for this geometry
-bool layout_single(const Geom& g);  // true if epl_layout does
 // K1 and K2 only: histograms and the prefix scans, left in the workspace for route_finalize_kernel.
 hipError_t launch_layout_counts(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* send_cnt, int32_t* rank_cnt,
                                 int32_t* tok_nranks, int32_t* num_invalid, hipStream_t stream);

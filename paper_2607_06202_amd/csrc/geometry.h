@@ -63,6 +63,47 @@ inline Geom make_geom(int R, int E, int k, int Tr) {
   return g;
 }
 
+// ------------------------------------------------------------------------ layouts in one launch
+// The one-launch layout (small.hip) counts all T*k ids in every workgroup and deduplicates each source
+// rank's earlier tokens again, so it is used only up to these sizes; larger layouts take three
+// launches. Whole layer of 2048 columns, layout and dispatch in one launch against three: 16K pairs
+// on 32 ranks 35.9 / 39.2 us, 24K 56.2 / 55.2, 32K 71.6 / 69.2. The rank limit keeps the second pass
+// short: 16K pairs on one rank took 39.7 / 37.5 us, 16K of top-1 67.6 / 44.2, 12K on two ranks
+// 29.2 / 32.1.
+constexpr int64_t kSingleMaxPairs = 16384;     // T*k
+constexpr int64_t kSingleMaxRankPairs = 4096;  // Tr*k
+// Bound on 9 E + 6 R for epl_layout alone, whose launch count (epl_layout_launches) it is part of.
+// epl_layout_dispatch has no such bound: 4K pairs on 1024 ranks of one expert take 26.6 us per layer in
+// one launch, 51.9 in three.
+constexpr int64_t kSingleMaxTable = 12287;
+
+inline bool small_layout(const Geom& g) {
+  return g.T * g.k <= kSingleMaxPairs && (int64_t)g.Tr * g.k <= kSingleMaxRankPairs;
+}
+
+inline bool layout_single(const Geom& g) {  // true if epl_layout runs as one launch for this geometry
+  return small_layout(g) && 9 * (int64_t)g.E + 6 * g.R <= kSingleMaxTable;
+}
+
+// Whether epl_layout_dispatch takes one launch for the layout and its rows (small.hip), or the rows a second
+// one. Every group of tokens counts all ids again and then sends with four waves, so many tokens are better
+// sent by the row kernel. Layout, dispatch and combine, speed in one launch / in two against a layout whose
+// workgroups walked each token's choices, followed by the row kernel; bf16 rows of 128 columns on 4 ranks:
+// top-1 of 2816 tokens 1.21 / 1.15, 4096 1.04 / 1.14, 8192 0.74 / 1.05, 16384 0.78 / 1.00; top-4 of 2816 tokens
+// 1.05 / 1.08, 4096 0.75 / 1.02; top-5 of 2816 1.01 / 1.07. T*T*k stands for the ids that all groups count.
+// fp8 rows are quantised a 1024-column pass to a wave, at an occupancy that suits counting and not
+// quantising: top-2 on 4 ranks, 1536 tokens of 3072 columns 1.10 / 1.09, 2048 tokens 0.96 / 1.09; top-6,
+// 1536 x 3072 0.97 / 1.05; top-4, 2048 x 4096 0.93 / 1.02; top-8, 1536 x 7168 1.07 / 1.03.
+constexpr int64_t kSmallSendTokens = 2816;
+constexpr int64_t kSmallSendCounts = 1 << 25;  // T*T*k
+constexpr int64_t kSmallSendPasses = 3072;     // fp8, rows of fewer passes than a group has waves: tokens * passes
+constexpr int64_t kSmallSendWide = 1536;       // fp8, wider rows: tokens
+inline bool small_dispatch(const Geom& g, int H, bool fp8) {
+  if (!small_layout(g) || g.T > kSmallSendTokens || g.T * g.T * g.k > kSmallSendCounts) return false;
+  const int passes = (H + 1023) / 1024;
+  return !fp8 || g.T <= (passes < kLayoutWaves ? kSmallSendPasses / passes : kSmallSendWide);
+}
+
 // ------------------------------------------------------------------------ layouts in two launches
 // route_count and route_place (layout.hip), for layouts of few chunks.
 constexpr int kPlaceMaxChunks = 512;

@@ -348,14 +348,6 @@ __global__ void __launch_bounds__(kLayoutThreads)
 }
 
 // ------------------------------------------------------------------------------------ host
-bool small_layout(const Geom& g) {
-  return g.T * g.k <= kSingleMaxPairs && (int64_t)g.Tr * g.k <= kSingleMaxRankPairs;
-}
-
-bool layout_single(const Geom& g) {
-  return small_layout(g) && 9 * (int64_t)g.E + 6 * g.R <= kSingleMaxTable;
-}
-
 static size_t finalize_lds_bytes(const Geom& g) {
   return sizeof(int32_t) * ((size_t)(g.E + 1) + g.E + g.R + (size_t)kLayoutWaves * (g.E + g.R));
 }

@@ -79,7 +79,12 @@ __device__ __forceinline__ int count_pairs(const int32_t* __restrict__ idx, int 
 
 // first[d] += the tokens among src's first nt that have a valid pair on destination rank d. Each
 // wave takes tpw whole tokens at a time, one lane per pair; a pair counts if it is the lowest lane
-// of its token with its rank.
+// of its token with its rank. MERGE adds once per wave and rank: with one or two (rank, choice) combinations
+// most lanes of a wave would add to one word, and adds to one LDS word are served one after another (layout of
+// 4096 tokens, top-1 on one rank: 11.1 us -> 8.3; with more ranks or choices the ballot costs more than it saves,
+// 16384 tokens on 4 ranks 11.8 -> 12.7).
+constexpr int kMergeMax = 2;  // R * k
+template <bool MERGE>
 __device__ __forceinline__ void count_first_pairs(const SmallArgs& A, const int32_t* __restrict__ src, int nt,
                                                   int32_t* first) {
   constexpr int kAhead = 4;  // loads in flight
@@ -99,8 +104,14 @@ __device__ __forceinline__ void count_first_pairs(const SmallArgs& A, const int3
       if (p >= np) break;  // wave-uniform
       const bool valid = in && p + lane < np && (unsigned)e[q] < (unsigned)G.E;
       const int d = valid ? small_div(e[q], G.inv_El) : 0;
-      const uint64_t same = match_key(valid, d, G.rbits) & mine;
-      if (valid && __builtin_ctzll(same) == lane) atomicAdd(&first[d], 1);
+      const uint64_t same = match_key(valid, d, G.rbits);
+      const bool is_first = valid && __builtin_ctzll(same & mine) == lane;
+      if constexpr (MERGE) {
+        const uint64_t firsts = same & __ballot(is_first);
+        if (is_first && __builtin_ctzll(firsts) == lane) atomicAdd(&first[d], __popcll(firsts));
+      } else if (is_first) {
+        atomicAdd(&first[d], 1);
+      }
     }
   }
 }
@@ -137,7 +148,7 @@ __device__ __forceinline__ int place_group(const SmallArgs& A, int64_t g0, int n
   return row;
 }
 
-template <int SEND, int VPL>
+template <int SEND, int VPL, bool MERGE>
 __global__ void __launch_bounds__(kLayoutThreads) route_single_kernel(SmallArgs A) {
   extern __shared__ int32_t lds[];
   __shared__ int32_t scratch[kLayoutWaves];
@@ -177,7 +188,7 @@ __global__ void __launch_bounds__(kLayoutThreads) route_single_kernel(SmallArgs 
   for (int i = tid; i < 3 * G.E + G.R; i += kLayoutThreads) lds[i] = 0;
   __syncthreads();
   const int inval = count_pairs(A.idx, n, G.E, a0, meta ? a0 + np : n, h);
-  count_first_pairs(A, rank_ids, meta ? G.Tr : t0, first);
+  count_first_pairs<MERGE>(A, rank_ids, meta ? G.Tr : t0, first);
   __syncthreads();
   {
     const int per = (G.E + kLayoutThreads - 1) / kLayoutThreads;
@@ -276,11 +287,19 @@ static SmallArgs small_args(const Geom& g, const int32_t* idx, const epl_layout_
 
 static size_t small_lds(const Geom& g) { return sizeof(int32_t) * ((size_t)4 * g.E + g.R + 1); }
 
-hipError_t launch_small_layout(const Geom& g, const int32_t* idx, const epl_layout_buffers& L, hipStream_t stream) {
-  const SmallArgs A = small_args(g, idx, L, 0);
-  hipLaunchKernelGGL((route_single_kernel<kSendNone, 1>), dim3(g.R * (1 + A.NG)), dim3(kLayoutThreads), small_lds(g),
-                     stream, A);
+template <int SEND, int VPL>
+static hipError_t launch_single(const SmallArgs& A, hipStream_t stream) {
+  const Geom& g = A.G;
+  const dim3 grid(g.R * (1 + A.NG)), block(kLayoutThreads);
+  if (g.R * g.k <= kMergeMax)
+    hipLaunchKernelGGL((route_single_kernel<SEND, VPL, true>), grid, block, small_lds(g), stream, A);
+  else
+    hipLaunchKernelGGL((route_single_kernel<SEND, VPL, false>), grid, block, small_lds(g), stream, A);
   return hipGetLastError();
+}
+
+hipError_t launch_small_layout(const Geom& g, const int32_t* idx, const epl_layout_buffers& L, hipStream_t stream) {
+  return launch_single<kSendNone, 1>(small_args(g, idx, L, 0), stream);
 }
 
 hipError_t launch_small_layout_dispatch(const Geom& g, const int32_t* idx, const epl_layout_buffers& L, const void* x,
@@ -296,16 +315,10 @@ hipError_t launch_small_layout_dispatch(const Geom& g, const int32_t* idx, const
   A.pv = fp8 ? pitch / 16 : pitch / 8;
   A.chunks = pieces;
   A.cap = cap;
-  const dim3 grid(g.R * (1 + A.NG)), block(kLayoutThreads);
-  if (fp8) {
-    hipLaunchKernelGGL((route_single_kernel<kSendFp8, 1>), grid, block, small_lds(g), stream, A);
-  } else if (g.T * pieces >= kSmallWideUnits) {
-    hipLaunchKernelGGL((route_single_kernel<kSendBf16, kBf16VPL>), grid, block, small_lds(g), stream, A);
-  } else {
-    A.chunks = (nv + kWave - 1) / kWave;
-    hipLaunchKernelGGL((route_single_kernel<kSendBf16, 1>), grid, block, small_lds(g), stream, A);
-  }
-  return hipGetLastError();
+  if (fp8) return launch_single<kSendFp8, 1>(A, stream);
+  if (g.T * pieces >= kSmallWideUnits) return launch_single<kSendBf16, kBf16VPL>(A, stream);
+  A.chunks = (nv + kWave - 1) / kWave;
+  return launch_single<kSendBf16, 1>(A, stream);
 }
 
 }  // namespace epl

@@ -31,6 +31,10 @@ int place_sum_counted(int R, int E, int k, int Tr) {
   return (int)std::min<int64_t>(*std::max_element(sum, sum + epl::kPlaceRows), INT_MAX);
 }
 
+int small_dispatch(int R, int E, int k, int Tr, int H, int fp8) {
+  return epl::small_dispatch(epl::make_geom(R, E, k, Tr), H, fp8 != 0);
+}
+
 unsigned unit_grid(int64_t units, int per_group, int threads) { return epl::unit_grid(units, per_group, threads); }
 
 }  // extern "C"

@@ -1,9 +1,9 @@
-"""epl_layout_dispatch in one launch (T*k <= 16384 and Tr*k <= 4096) against the CPU oracle, bit for
-bit, at the edges of its groups: a wave of exactly 64 pairs and of fewer (k that does not divide
-64), one token per group, ragged last groups, few tokens (1 KiB pieces) and many (4 KiB pieces),
-ragged rows, one rank, ranks without tokens, 1024 ranks of one expert (beyond the one-launch limit of
-epl_layout alone), ids at 16-byte alignment and 4 bytes past it. Rows past the valid pairs, and the
-arrays past them, keep their fill."""
+"""epl_layout_dispatch of small layouts (T*k <= 16384 and Tr*k <= 4096), in one launch or with the rows in a
+second one, against the CPU oracle, bit for bit, at the edges of the layout's groups: a wave of exactly 64 pairs
+and of fewer (k that does not divide 64), one token per group, ragged last groups, few tokens (1 KiB pieces)
+and many (4 KiB pieces), the most tokens that are sent in one launch and more, ragged rows, one rank and one choice,
+ranks without tokens, 1024 ranks of one expert (beyond the one-launch limit of epl_layout alone), ids at
+16-byte alignment and 4 bytes past it. Rows past the valid pairs, and the arrays past them, keep their fill."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,13 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("R,E,k,Tr,H,payload", [
     (32, 256, 8, 64, 512, "bf16"),      # 16384 pairs: the limit
-    (4, 64, 1, 4096, 64, "bf16"),       # top-1, 4096 pairs per rank: groups of 64 tokens
+    (4, 64, 1, 4096, 64, "bf16"),       # top-1, 4096 pairs per rank: groups of 64 tokens, rows in a second launch
+    (4, 64, 1, 704, 1032, "bf16"),      # the most tokens sent in one launch
+    (1, 8, 1, 2816, 264, "bf16"),       # one rank and one choice: every lane adds to one word
+    (1, 8, 2, 1201, 72, "bf16"),        # one rank, two choices
+    (2, 6, 1, 1000, 512, "bf16"),       # two ranks of one choice
+    (2, 6, 1, 1025, 3072, "fp8"),       # 2050 tokens of three passes: rows in a second launch
+    (1, 4, 1, 4096, 128, "fp8"),        # 4096 tokens on one rank
     (5, 35, 7, 61, 2056, "bf16"),       # 63 of 64 lanes, ragged groups, a second piece of one vector
     (3, 96, 32, 40, 1032, "bf16"),      # two tokens per wave
     (2, 46, 23, 9, 8, "bf16"),          # 46 lanes, one vector per row
@@ -31,7 +37,7 @@ pytestmark = pytest.mark.gpu
     (4, 16, 2, 0, 256, "bf16"),         # no tokens
 ])
 @pytest.mark.parametrize("aligned", [True, False])
-def test_one_launch_layout_dispatch(R, E, k, Tr, H, payload, aligned):
+def test_small_layout_dispatch(R, E, k, Tr, H, payload, aligned):
     dev = device()
     T = R * Tr
     cfg = epl.config(R, E, k, H, Tr, payload)

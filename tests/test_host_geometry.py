@@ -95,3 +95,14 @@ def test_place_kernel_chunks(geo):
     assert chunks(geo, 1, 256, 8, 61440) == dict(CT=128, NC=480, nblk=480, pCT=128, pNC=480, pnblk=480, sum=61440, place=1)
     assert not chunks(geo, 1, 256, 8, 61441)["place"]   # 481 chunks: sums of up to 65536
     assert chunks(geo, 241, 241, 8, 130)["place"]       # longer chunks than the layout's own
+
+
+@pytest.mark.parametrize("R,E,k,Tr,H,fp8,one", [
+    (16, 128, 8, 128, 2048, 0, 1), (32, 160, 8, 37, 5120, 0, 1), (4, 16, 2, 128, 256, 0, 1),  # decode shapes
+    (16, 128, 8, 128, 2048, 1, 0), (16, 128, 8, 64, 7168, 1, 1), (8, 64, 4, 192, 2048, 1, 1), (8, 64, 4, 256, 4096, 1, 0),
+    (4, 64, 1, 704, 128, 0, 1), (4, 64, 1, 705, 128, 0, 0),    # 2816 and 2820 tokens
+    (4, 64, 1, 4096, 128, 0, 0), (64, 64, 2, 128, 128, 0, 0),  # where one launch took up to 1.47 times as long
+    (1, 8, 1, 4096, 2048, 1, 0), (8, 64, 5, 352, 128, 0, 0)])
+def test_small_layers_whose_rows_go_with_the_layout(geo, R, E, k, Tr, H, fp8, one):
+    """The layers that take one launch, on both sides of each bound of the rule."""
+    assert geo.small_dispatch(R, E, k, Tr, H, fp8) == one
