@@ -151,6 +151,22 @@ inline unsigned unit_grid(int64_t units, int per_group, int threads) {
   return (unsigned)std::min<int64_t>((units + per_group - 1) / per_group, UINT32_MAX / threads);
 }
 
+// ------------------------------------------------------------------------ scheduled dispatch
+// Which form of the bf16 kernel sends `slices` slices of `pairs` pairs in all, in `chunks` 4 KiB units a row:
+// the long one (four workgroups per compute unit, the next unit's loads in flight under this one's stores) or
+// the short one (as many workgroups as fit, one unit at a time). A workgroup finds its slice before it
+// sends, and only others on its compute unit hide that, so a slice has to be long; and with more workgroups
+// than run at once their rows must not fit the 256 MB memory-side cache, or how writes spread over the memory
+// does not matter. us in the long / short form: 64 ranks x 128 tokens x 7168 columns, 64 workers 211 / 268;
+// 16 x 128 x 2048, 32 workers 16.4 / 17.0, 128 workers 17.2 / 15.0; 256 x 16 x 1024, 64 workers 60 / 35; 256 x
+// 32 x 512, 8 workers 22.4 / 16.8; 32 x 64 x 5120, 48 workers 33.9 / 28.1.
+constexpr int kLongSliceUnits = 32;
+constexpr int kLongSlicesAtOnce = 1024;        // four workgroups on each of 256 compute units
+constexpr int64_t kLongRowBytes = 256 << 20;
+inline bool long_slices(int64_t pairs, int H, int chunks, int64_t slices) {
+  return pairs * chunks >= slices * kLongSliceUnits && (slices <= kLongSlicesAtOnce || pairs * H * 2 >= kLongRowBytes);
+}
+
 // ------------------------------------------------------------------------ one-launch layers
 constexpr int kFewChoices = 2;    // up to this many choices a wave has little to write, and more waves are run
 constexpr int kSendBatch = 4;     // most tokens a send workgroup takes at a time: one per wave

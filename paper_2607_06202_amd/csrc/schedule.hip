@@ -148,18 +148,19 @@ __global__ void __launch_bounds__(kScheduleThreads)
 // batches of one per thread: each thread locates its position (Algorithm 1's lookup over the
 // remapped cumulative counts), takes the pair's packed row seg_off[e][s] + offset and its token
 // recv_src[row], and shares both through LDS; the waves then copy the batch's rows, one
-// (row, 4 KiB column chunk) unit per wave at a time, the next unit's loads in flight under this one's
-// stores. bf16 is held at 4 waves per SIMD: few scattered writes at a time spread better over the memory.
+// (row, 4 KiB column chunk) unit per wave at a time. Long bf16 slices (long_slices) have the next unit's loads in
+// flight under this one's stores, at 4 waves per SIMD: few scattered writes at a time spread better over the
+// memory. Short ones send one unit at a time from all waves that fit: what bounds them is finding the slice.
 // Whole layer, one unit at a time with 5 waves / two units with any number / two units with 4 waves:
 // 128 ranks of 64 tokens with 64 workers 410 / 406 / 404 us, 64 ranks of 128 tokens with 32 workers
 // 495 / 495 / 452, with 128 workers 413 / 409 / 405.5, 16 ranks of 2048 columns 59.9 / 59.1 / 59.0. 1 KiB
 // units, the plain dispatch's, took 414-561 us on the first, 2 KiB units 406-491.
-// FP8: each row is quantised as it is copied, by the fp8 dispatch's unit (token, 1024-element pass)
+// fp8: each row is quantised as it is copied, by the fp8 dispatch's unit (token, 1024-element pass)
 // with one destination; units per row is then the number of passes.
-constexpr int scheduled_max_waves(bool fp8) { return fp8 ? 8 : 4; }
-template <bool FP8>
+constexpr int kSlicesFp8 = 0, kSlicesLong = 1, kSlicesShort = 2;
+template <int FORM>
 __global__ void __launch_bounds__(kScheduleThreads)
-    __attribute__((amdgpu_waves_per_eu(FP8 ? 1 : 4, scheduled_max_waves(FP8))))
+    __attribute__((amdgpu_waves_per_eu(FORM == kSlicesLong ? 4 : 1, FORM == kSlicesLong ? 4 : 8)))
     dispatch_scheduled_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ send_cnt,
                               const int32_t* __restrict__ seg_off, const int32_t* __restrict__ recv_src,
                               u32x4* __restrict__ recv, float* __restrict__ recv_scale, int R, int E, int rows, int n,
@@ -194,7 +195,7 @@ __global__ void __launch_bounds__(kScheduleThreads)
     __syncthreads();
     const int units = nb * chunks;
     constexpr int kWaves = kScheduleThreads / kWave;
-    if constexpr (FP8) {
+    if constexpr (FORM == kSlicesFp8) {
       for (int u = threadIdx.x / kWave; u < units; u += kWaves) {
         const int q = u / chunks;
         const int row = row_lds[q];
@@ -214,10 +215,13 @@ __global__ void __launch_bounds__(kScheduleThreads)
       };
       u32x4 buf[kBf16VPL];
       int u = threadIdx.x / kWave;
-      if (u < units) load_unit(u, buf);
+      if (FORM == kSlicesLong && u < units) load_unit(u, buf);
       for (; u < units; u += kWaves) {
         u32x4 next[kBf16VPL];
-        if (u + kWaves < units) load_unit(u + kWaves, next);
+        if constexpr (FORM == kSlicesShort)
+          load_unit(u, buf);
+        else if (u + kWaves < units)
+          load_unit(u + kWaves, next);
         const int q = u / chunks;
         const int row = __builtin_amdgcn_readfirstlane(row_lds[q]);
         const int g = __builtin_amdgcn_readfirstlane(src_lds[q]);
@@ -229,8 +233,10 @@ __global__ void __launch_bounds__(kScheduleThreads)
             if (v < nv) store_row_policy<kCachePolicySc1>(buf[i], recv + (int64_t)row * pv, nv, v);
           }
         }
+        if constexpr (FORM == kSlicesLong) {
 #pragma unroll
-        for (int i = 0; i < kBf16VPL; ++i) buf[i] = next[i];
+          for (int i = 0; i < kBf16VPL; ++i) buf[i] = next[i];
+        }
       }
     }
     __syncthreads();  // the batch's rows are consumed before the next batch overwrites them
@@ -255,10 +261,13 @@ hipError_t launch_dispatch_scheduled(const void* x, const int32_t* send_cnt, con
   const u32x4* xv = static_cast<const u32x4*>(x);
   u32x4* rv = static_cast<u32x4*>(recv);
   if (fp8)
-    hipLaunchKernelGGL(dispatch_scheduled_kernel<true>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt, seg_off,
-                       recv_src, rv, recv_scale, R, E, rows, n, T, k, H, pitch, chunks, cap);
+    hipLaunchKernelGGL(dispatch_scheduled_kernel<kSlicesFp8>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
+                       seg_off, recv_src, rv, recv_scale, R, E, rows, n, T, k, H, pitch, chunks, cap);
+  else if (long_slices(T * k, H, chunks, (int64_t)R * n))
+    hipLaunchKernelGGL(dispatch_scheduled_kernel<kSlicesLong>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
+                       seg_off, recv_src, rv, nullptr, R, E, rows, n, T, k, H, pitch, chunks, cap);
   else
-    hipLaunchKernelGGL(dispatch_scheduled_kernel<false>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
+    hipLaunchKernelGGL(dispatch_scheduled_kernel<kSlicesShort>, grid, dim3(kScheduleThreads), 0, stream, xv, send_cnt,
                        seg_off, recv_src, rv, nullptr, R, E, rows, n, T, k, H, pitch, chunks, cap);
   return hipGetLastError();
 }

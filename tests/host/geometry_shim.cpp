@@ -35,6 +35,10 @@ int small_dispatch(int R, int E, int k, int Tr, int H, int fp8) {
   return epl::small_dispatch(epl::make_geom(R, E, k, Tr), H, fp8 != 0);
 }
 
+int long_slices(int64_t pairs, int H, int64_t slices) {
+  return epl::long_slices(pairs, H, (H / 8 + 255) / 256, slices);
+}
+
 unsigned unit_grid(int64_t units, int per_group, int threads) { return epl::unit_grid(units, per_group, threads); }
 
 }  // extern "C"

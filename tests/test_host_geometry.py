@@ -106,3 +106,14 @@ def test_place_kernel_chunks(geo):
 def test_small_layers_whose_rows_go_with_the_layout(geo, R, E, k, Tr, H, fp8, one):
     """The layers that take one launch, on both sides of each bound of the rule."""
     assert geo.small_dispatch(R, E, k, Tr, H, fp8) == one
+
+
+@pytest.mark.parametrize("R,k,Tr,H,workers,long", [
+    (128, 8, 64, 7168, 64, 1), (64, 8, 128, 7168, 32, 1), (16, 8, 128, 2048, 32, 1),
+    (128, 8, 64, 7168, 96, 0), (16, 8, 128, 2048, 48, 0), (64, 8, 64, 4096, 48, 0),  # fewer than 32 units a slice
+    (256, 8, 32, 512, 8, 0), (32, 8, 64, 5120, 48, 0),  # more slices than run at once, rows in the cache
+    (256, 8, 16, 1024, 64, 0), (64, 2, 64, 512, 64, 0)])
+def test_scheduled_slices_form(geo, R, k, Tr, H, workers, long):
+    """Both sides of each bound; the last two lost 1.3 and 1.5 times in the long form."""
+    geo.long_slices.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int64]
+    assert geo.long_slices(R * Tr * k, H, R * workers) == long
