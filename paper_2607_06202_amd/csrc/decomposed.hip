@@ -117,10 +117,12 @@ __device__ __forceinline__ bool workgroup_wait(int32_t* word, int target, int64_
 // thread 0 of the last one. Adds to one address are served one after another, so where all workgroups
 // arrive together they add to kLeaves words (word `leaf` of each synchronisation line) and the last of
 // each leaf adds to the root: the counts of 256 workgroups meet 3-4 us after the last has finished, 6-7
-// with one counter. With kNoLeaf they add to the root (arrivals spread by more than an add takes: the
-// second level would only cost its round trip, 3 us).
+// with one counter. Few workgroups, and all with kNoLeaf, add to the root (arrivals spread by more than an add
+// takes: the second level would only cost its round trip; layout and dispatch of 32 tokens on 16 ranks 28.6 us with
+// it, 25.9 without).
 constexpr int kLeaves = kSyncWords / kSyncStride;
-__device__ __forceinline__ int leaf_count(int n) { return min(n, kLeaves); }
+constexpr int kLeafFrom = 128;  // fewer workgroups add to the root
+__device__ __forceinline__ int leaf_count(int n) { return n < kLeafFrom ? n : kLeaves; }
 __device__ __forceinline__ bool workgroup_publish(int32_t* sync, int root, int leaf, int i, int n) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
@@ -128,7 +130,7 @@ __device__ __forceinline__ bool workgroup_publish(int32_t* sync, int root, int l
   auto add = [&](int word) {
     return __hip_atomic_fetch_add(&sync[word], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (leaf == kNoLeaf) return add(root) == n - 1;
+  if (leaf == kNoLeaf || n < kLeafFrom) return add(root) == n - 1;
   const int l = i % kLeaves;
   if (add(l * kSyncStride + leaf) != (n - l + kLeaves - 1) / kLeaves - 1) return false;
   return add(root) == leaf_count(n) - 1;
@@ -234,23 +236,29 @@ __device__ __forceinline__ uint64_t wave_xor64(uint64_t h) {
 
 __device__ __forceinline__ uint64_t epoch_salt(uint64_t epoch) { return mix64(epoch ^ 0x5851F42D4C957F2Dull); }
 
+// The wave's index in its workgroup; the compiler does not see by itself that it is the same in all lanes.
+template <int SYNC, int FORM>
+__device__ __forceinline__ int wave_index() {
+  const int w = threadIdx.x / kWave;
+  return scalar_wave(FORM, SYNC != kDafNone) ? __builtin_amdgcn_readfirstlane(w) : w;
+}
+
 // Sends the batches j, j + ns, ... of A.batch consecutive tokens, after waiting for the offsets once
 // the first loads are issued. One wave places each token of the batch (its rows go to the others
 // through LDS), then the four waves take the batch's (token, 1 KiB column chunk) units in turn. A token
 // is placed once, and rows are written in the 1 KiB pieces that spread best over the memory. A wave
-// loads kSendAhead units together: waiting for a load that was issued behind stores is waiting for
-// those stores. Returns false if it gave up.
+// loads AHEAD units together (send_ahead). Returns false if it gave up.
 // Against one 4 KiB unit per wave at a time, each with a placement of its own, whole layer: 16 ranks x
-// 128 tokens x 2048 columns 49.0 -> 44.9 us, 32 x 64 x 7168 113.0 -> 107.8, 64 x 128 x 7168 411 -> 408.
-// With two units loaded together 47.1, 116 and 413 (at three workgroups per compute unit; four units
-// there 45.0, 112, 412); with the next unit's load in flight under the stores 51, 125 and 410.
+// 128 tokens x 2048 columns 49.0 -> 44.9 us, 32 x 64 x 7168 113.0 -> 107.8, 64 x 128 x 7168 411 -> 408; with the
+// next unit's load in flight under the stores 51, 125 and 410.
 // Measured against handing out batches of units from a launch-wide counter, with the count
 // workgroups joining once their counting was done: that was slower (decode 416.7 against
 // 396.8 us per layer, the Qwen3-30B shape 61.2 against 50.7 us), the counter's atomics serialising.
-template <int SYNC>
+template <int SYNC, int FORM>
 __device__ __forceinline__ bool send_role(const DecomposedArgs& A, int j, int32_t* lds, int32_t* flag) {
   const int lane = threadIdx.x % kWave;
-  const int w = threadIdx.x / kWave;
+  constexpr int AHEAD = send_ahead(FORM, SYNC != kDafNone);
+  const int w = wave_index<SYNC, FORM>();
   const int k = A.F.G.k;
   const int nv = A.nv;
   int32_t* rows_lds = lds;  // [kWavesPerBlock][k]
@@ -261,10 +269,10 @@ __device__ __forceinline__ bool send_role(const DecomposedArgs& A, int j, int32_
   for (int64_t g0 = (int64_t)j * A.batch; g0 < A.F.G.T; g0 += (int64_t)A.ns * A.batch) {
     const int ntok = (int)std::min<int64_t>(A.batch, A.F.G.T - g0);  // <= kWavesPerBlock
     const int units = ntok * A.cchunks;
-    u32x4 buf[kSendAhead];
-    auto load_units = [&](int u0) {  // units u0, u0 + 4, ... of this wave; no branch, past the last an empty resource
+    u32x4 buf[AHEAD];
+    auto load_units = [&](int u0) {  // units u0, u0 + 4, ... of this wave; past the last an empty resource, not a branch
 #pragma unroll
-      for (int q = 0; q < kSendAhead; ++q) {
+      for (int q = 0; q < AHEAD; ++q) {
         const int u = min(u0 + q * kWavesPerBlock, units - 1);
         const int tl = u / A.cchunks;
         const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(
@@ -285,10 +293,10 @@ __device__ __forceinline__ bool send_role(const DecomposedArgs& A, int j, int32_
       if (lane < k) rows_lds[w * k + lane] = r;
     }
     __syncthreads();
-    for (int u0 = w; u0 < units; u0 += kSendAhead * kWavesPerBlock) {
+    for (int u0 = w; u0 < units; u0 += AHEAD * kWavesPerBlock) {
       if (u0 != w) load_units(u0);
 #pragma unroll
-      for (int q = 0; q < kSendAhead; ++q) {
+      for (int q = 0; q < AHEAD; ++q) {
         const int u = u0 + q * kWavesPerBlock;
         if (u >= units) break;
         const int tl = u / A.cchunks;
@@ -336,17 +344,18 @@ __device__ __forceinline__ u32x4 gather_vec(const u32x4* y, int row, int pv, int
 // bf16 round-to-nearest-even, as the combine kernel does.
 //
 // What bounds it is latency: a row's load is a round trip to memory (device-scope, past the L2), and
-// placing a token costs about as much again. So all of a chunk's rows (up to kAhead at a time) are
+// placing a token costs about as much again. So all of a chunk's rows (up to kAhead at a time; two with few
+// choices, where the other six would be empty loads and checks) are
 // loaded before any is checked, a wave keeps its token for as many chunks as leave every wave a task, and
 // every workgroup of the launch combines. Against combine workgroups of their own that loaded one row after
 // another, whole layer: 16 ranks x 128 tokens x 2048 columns sentinel 68.9 -> 55.1 us, flag 75.4 -> 46.5,
 // checksum 75.4 -> 60.0; 32 x 64 x 7168 sentinel 192 -> 156; 64 x 128 x 7168 967 -> 630.
-template <int SYNC>
+template <int SYNC, int FORM>
 __device__ __forceinline__ void combine_role(const DecomposedArgs& A, int ci, int32_t* lds) {
-  constexpr int kAhead = 8;
+  constexpr int kAhead = FORM == kFormFew ? kFewChoices : 8;
   const Geom& G = A.F.G;
   const int lane = threadIdx.x % kWave;
-  const int w = threadIdx.x / kWave;
+  const int w = wave_index<SYNC, FORM>();
   const int k = G.k;
   int32_t* hist = lds + kWavesPerBlock * EPL_MAX_TOPK + w * (G.E + G.R);
   const int nv = A.nv;
@@ -468,6 +477,82 @@ __device__ __forceinline__ void combine_role(const DecomposedArgs& A, int ci, in
   if (!arrived && lane == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
 }
 
+// The split form's combine: one (token, 1 KiB column chunk) per wave at a time, its rows one after another, each
+// loaded until it is there and folded (and, for Sentinel Polling, reset) before the next. The task at hand is
+// short, and so is the code (see send_ahead).
+template <int SYNC>
+__device__ __forceinline__ void combine_rows(const DecomposedArgs& A, int ci, int groups, int32_t* lds) {
+  const Geom& G = A.F.G;
+  const int lane = threadIdx.x % kWave;
+  const int w = wave_index<SYNC, kFormSplit>();
+  const int k = G.k;
+  int32_t* hist = lds + kWavesPerBlock * EPL_MAX_TOPK + w * (G.E + G.R);
+  const int nv = A.nv;
+  const int64_t units = G.T * A.cchunks;
+  const int64_t stride = (int64_t)groups * kWavesPerBlock;
+  const u32x4* y = A.recv;
+  const uint64_t salt = epoch_salt(A.epoch);
+  for (int64_t u = (int64_t)ci * kWavesPerBlock + w; u < units; u += stride) {
+    const int64_t g = u / A.cchunks;
+    const int c = (int)(u - g * A.cchunks);
+    const int rows = token_rows<false>(A.F, g, false, hist, lane);
+    const int v = c * kWave + lane;
+    const bool on = v < nv;
+    const int vl = min(v, nv - 1);
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    for (int j = 0; j < k; ++j) {
+      const int row = __builtin_amdgcn_readlane(rows, j);
+      if (row < 0) continue;
+      const float wj = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, A.topk_w[g * k + j])));
+      const uint64_t* mark = A.marks + (int64_t)row * A.cchunks + c;
+      u32x4 val;
+      // Loads the lane's vector; whether the whole chunk of the row has arrived (wave-uniform).
+      auto load = [&] {
+        if constexpr (SYNC == kDafFlag) {
+          if (ld64_dev(mark) != A.epoch) return false;
+          val = gather_vec(y, row, A.pv, nv, vl);
+          return true;
+        } else if constexpr (SYNC == kDafChecksum) {
+          const uint64_t m = ld64_dev(mark);
+          val = gather_vec(y, row, A.pv, nv, vl);
+          return (wave_xor64(lane_hash(val, on, lane)) ^ salt) == m;
+        } else {
+          val = gather_vec(y, row, A.pv, nv, vl);
+          return __ballot(holds_sentinel(val)) == 0;
+        }
+      };
+      if (!load()) {
+        const int64_t t0 = wall_clock64();
+        do {
+          if (wall_clock64() - t0 > A.spin_ticks) {  // wave-uniform: stop, store nothing more
+            if (lane == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
+            return;
+          }
+          __builtin_amdgcn_s_sleep(1);
+        } while (!load());
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        acc[2 * i] = fmaf(wj, bf16lo_to_f32(val[i]), acc[2 * i]);
+        acc[2 * i + 1] = fmaf(wj, bf16hi_to_f32(val[i]), acc[2 * i + 1]);
+      }
+      if (SYNC == kDafSentinel && on) {  // consumed: back to the sentinel for the next layer
+        const u32x4 s = {kSentinelPair, kSentinelPair, kSentinelPair, kSentinelPair};
+        store_row_policy<kCachePolicySc1>(s, A.recv + (int64_t)row * A.pv, nv, v);
+      }
+    }
+    if (on) {
+      u32x4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) o[i] = f32x2_to_bf16x2(acc[2 * i], acc[2 * i + 1]);
+      const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(A.out + g * nv, 0, nv * 16, kBufferRsrcWord3);
+      __builtin_amdgcn_raw_buffer_store_b128(o, r, v * 16, 0, kCachePolicySc1Nt);
+    }
+  }
+}
+
 // The last workgroup to finish writes the status word and zeroes the synchronisation words. Every
 // other workgroup has passed all its waits by then.
 __device__ __forceinline__ void finish(const DecomposedArgs& A) {
@@ -478,8 +563,9 @@ __device__ __forceinline__ void finish(const DecomposedArgs& A) {
 }
 
 // Every workgroup of a layer variant goes on to combine when its own role is done: the whole device
-// sends first, and by the time a workgroup combines, most of what it gathers has arrived.
-template <int SYNC>
+// sends first, and by the time a workgroup combines, most of what it gathers has arrived. In the split form
+// the workgroups past the senders combine meanwhile.
+template <int SYNC, int FORM>
 __global__ void __launch_bounds__(kLayoutThreads) __attribute__((amdgpu_waves_per_eu(5)))
     decomposed_kernel(DecomposedArgs A) {
   static_assert(kDispatchThreads == kLayoutThreads, "both roles run in 256-thread workgroups");
@@ -496,13 +582,24 @@ __global__ void __launch_bounds__(kLayoutThreads) __attribute__((amdgpu_waves_pe
     count_role(A, (int)blockIdx.x, lds, red, scratch, seg_start, &flag);
     sends = A.ns > (int)gridDim.x - A.nc;
     j += (int)gridDim.x;  // after the send workgroups: gridDim - nc + i
-    if (sends || SYNC != kDafNone)
+    if (sends || (SYNC != kDafNone && FORM != kFormSplit))
       ready = workgroup_wait<true>(&A.sync[kSyncReady], A.ready_target, A.spin_ticks, &flag);
   }
-  if (sends && ready) ready = send_role<SYNC>(A, j, lds, &flag);
-  if constexpr (SYNC != kDafNone) {
+  if constexpr (FORM == kFormSplit) {
+    if (j >= A.ns) {  // also the count workgroups, whose j lies past the senders
+      sends = false;
+      if ((int)blockIdx.x >= A.nc) {
+        if (workgroup_wait<true>(&A.sync[kSyncReady], A.ready_target, A.spin_ticks, &flag))
+          combine_rows<SYNC>(A, j - A.ns, (int)gridDim.x - A.nc - A.ns, lds);
+        else if (threadIdx.x == 0)
+          atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
+      }
+    }
+  }
+  if (sends && ready) ready = send_role<SYNC, FORM>(A, j, lds, &flag);
+  if constexpr (SYNC != kDafNone && FORM != kFormSplit) {
     if (ready)
-      combine_role<SYNC>(A, (int)blockIdx.x, lds);
+      combine_role<SYNC, FORM>(A, (int)blockIdx.x, lds);
     else if (threadIdx.x == 0)
       atomicOr(&A.sync[kSyncStatus], kGaveUpCombine);
   }
@@ -512,19 +609,23 @@ __global__ void __launch_bounds__(kLayoutThreads) __attribute__((amdgpu_waves_pe
 // ------------------------------------------------------------------------ host
 namespace {
 
-void launch_variant(int sync, dim3 grid, dim3 block, size_t lds, hipStream_t stream, const DecomposedArgs& A) {
+typedef void (*DecomposedKernel)(DecomposedArgs);
+template <int SYNC>
+DecomposedKernel kernel_of_form(int form) {
+  if constexpr (SYNC != kDafNone) {
+    if (form == kFormSplit) return decomposed_kernel<SYNC, kFormSplit>;
+  } else {
+    if (form == kFormWide) return decomposed_kernel<SYNC, kFormWide>;
+  }
+  return form == kFormFew ? decomposed_kernel<SYNC, kFormFew> : decomposed_kernel<SYNC, kFormGeneral>;
+}
+
+DecomposedKernel kernel_of(int sync, int form) {
   switch (sync) {
-    case kDafSentinel:
-      hipLaunchKernelGGL(decomposed_kernel<kDafSentinel>, grid, block, lds, stream, A);
-      break;
-    case kDafFlag:
-      hipLaunchKernelGGL(decomposed_kernel<kDafFlag>, grid, block, lds, stream, A);
-      break;
-    case kDafChecksum:
-      hipLaunchKernelGGL(decomposed_kernel<kDafChecksum>, grid, block, lds, stream, A);
-      break;
-    default:
-      hipLaunchKernelGGL(decomposed_kernel<kDafNone>, grid, block, lds, stream, A);
+    case kDafSentinel: return kernel_of_form<kDafSentinel>(form);
+    case kDafFlag: return kernel_of_form<kDafFlag>(form);
+    case kDafChecksum: return kernel_of_form<kDafChecksum>(form);
+    default: return kernel_of_form<kDafNone>(form);
   }
 }
 
@@ -537,28 +638,19 @@ size_t decomposed_lds_bytes(const Geom& g) {
 
 }  // namespace
 
-template <int SYNC>
-static hipError_t occupancy(int* per_cu, size_t lds) {
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, decomposed_kernel<SYNC>, kLayoutThreads, lds);
-}
-
-static hipError_t occupancy_of(int sync, int* per_cu, size_t lds) {
-  switch (sync) {
-    case kDafSentinel: return occupancy<kDafSentinel>(per_cu, lds);
-    case kDafFlag: return occupancy<kDafFlag>(per_cu, lds);
-    case kDafChecksum: return occupancy<kDafChecksum>(per_cu, lds);
-    default: return occupancy<kDafNone>(per_cu, lds);
-  }
-}
-
 hipError_t plan_decomposed(const Geom& g, int H, int count_groups, int sync, DecomposedPlan* plan) {
-  int dev = 0, cus = 0, per_cu = 0;
+  int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e == hipSuccess) e = occupancy_of(sync, &per_cu, decomposed_lds_bytes(g));
   if (e != hipSuccess) return e;
-  *plan = split_decomposed(g, H, count_groups, sync, per_cu * cus, cus);
-  return hipSuccess;
+  for (int form = decomposed_form(g, H, sync);; form = joined_form(g, H, sync)) {
+    int per_cu = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel_of(sync, form), kLayoutThreads, decomposed_lds_bytes(g));
+    if (e != hipSuccess) return e;
+    *plan = split_decomposed(g, H, count_groups, sync, form, per_cu * cus, cus);
+    // A count_groups that leaves room for a single workgroup: it has to send and to combine.
+    if (form != kFormSplit || plan->grid <= plan->capacity) return hipSuccess;
+  }
 }
 
 hipError_t launch_decomposed(const Geom& g, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
@@ -605,7 +697,7 @@ hipError_t launch_decomposed(const Geom& g, const int32_t* idx, int32_t* ws, con
   A.spin_ticks = opts.spin_ticks;
   A.ready_target = opts.ready_target;
   const size_t lds = decomposed_lds_bytes(g);
-  launch_variant(sync, dim3(plan.grid), dim3(kLayoutThreads), lds, stream, A);
+  hipLaunchKernelGGL(kernel_of(sync, plan.form), dim3(plan.grid), dim3(kLayoutThreads), lds, stream, A);
   return hipGetLastError();
 }
 

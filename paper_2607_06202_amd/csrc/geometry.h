@@ -170,7 +170,6 @@ inline bool long_slices(int64_t pairs, int H, int chunks, int64_t slices) {
 // ------------------------------------------------------------------------ one-launch layers
 constexpr int kFewChoices = 2;    // up to this many choices a wave has little to write, and more waves are run
 constexpr int kSendBatch = 4;     // most tokens a send workgroup takes at a time: one per wave
-constexpr int kSendAhead = 4;     // 1 KiB units a send wave loads together (measured beside send_role)
 
 // How the layer variants' combine learns that a row chunk has arrived (Data-as-Flag):
 // kDafNone is the launch without a combine (layout and dispatch only).
@@ -179,8 +178,66 @@ constexpr int kDafSentinel = 1;   // Sentinel Polling: every element compared wi
 constexpr int kDafFlag = 2;       // Token-Flag Fusion: an epoch flag per 1 KiB chunk, stored after the chunk
 constexpr int kDafChecksum = 3;   // Data-for-Checksum: a salted hash per 1 KiB chunk, checked against the data
 
+// Forms of the kernel. In all but the split one every workgroup that sends goes on to combine; there the
+// workgroups past the senders only combine, a row at a time.
+constexpr int kFormGeneral = 0;
+constexpr int kFormFew = 1;    // up to kFewChoices choices: fewer loads together, less to compile and to fetch
+constexpr int kFormWide = 2;   // layout and dispatch of many long rows (see scalar_wave)
+constexpr int kFormSplit = 3;
+
+// 1 KiB units a send wave loads together. Waiting for a load that was issued behind stores is waiting for
+// those stores, so a wave loads several units before it stores any. Layout and dispatch, us per layer at 2 / 4 / 6
+// units: 32 ranks x 64 tokens x 7168 columns 111.4 / 108.4 / 105.7, 64 x 128 x 7168 407 / 408.5 / 407, 64 x 128 x 256 47.3 /
+// 47.0 / 48.9, 64 x 256 top-4 x 1024 84.0 / 83.7 / 85.9; top-1, 32 x 1024 x 256 71.7 / 74.2 / 77.2. The split form's code is fetched anew by every compute unit, which counts in layers
+// of 20 us: with 1 / 4 units ahead (24 and 29 KB of code) 512 tokens top-2 x 256 columns 16.3 / 17.0.
+constexpr int send_ahead(int form, bool layer) {
+  return form == kFormSplit ? 1 : form == kFormFew && !layer ? 2 : 4;
+}
+
+// Whether the send and combine roles hold the wave's index in their workgroup as a scalar, which makes the
+// loads of x single instructions, or in a vector register, which makes them loops over lanes. us with the
+// scalar / the vector, layout and dispatch: 64 ranks x 128 tokens x 7168 columns 409.8 / 408.3, but 64 x 256 top-4 x
+// 1024 83.7 / 87, 64 x 64 top-16 x 2048 123.7 / 128, 64 x 4 x 7168 31.0 / 32.9. In the general form of the layers it is a matter of
+// the shape: Sentinel, 32 x 64 x 7168 149 / 159, 16 x 128 x 2048 55.6 / 54.7, 32 x 64 top-4 x 512 27.1 / 26.8.
+constexpr bool scalar_wave(int form, bool layer) {
+  return form == kFormFew || form == kFormSplit || (form == kFormGeneral && !layer);
+}
+constexpr int kWideChunks = 8;
+constexpr int64_t kWideTokens = 2048;
+
+// Which form takes a layer. Against workgroups of their own for the combine, a whole device that sends and
+// then combines has more waves for each, but places every token twice in a row and overlaps nothing. Whole
+// layer, speed split / joined against the first form that this kernel had:
+// * short rows in several rounds of batches: top-1, 32 ranks x 1024 tokens x 256 columns, Sentinel 1.16 / 0.85,
+//   flag 1.31 / 1.08, checksum 1.15 / 1.05; top-3, 32 x 512 x 256 1.13 / 0.84, 1.21 / 1.11, 1.10 / 0.92; with two 1 KiB
+//   chunks the joined form wins (top-2, 32 x 1024 x 1024, Sentinel 1.17 / 1.23);
+// * few tokens: top-2, 4 x 128 x 256 1.00 / 0.84, 0.96 / 0.91, 1.01 / 0.97; top-4, 16 x 2 x 4992 0.96 / 0.76, 0.92 /
+//   0.86, 0.96 / 0.80; top-8, 8 x 16 x 2048 1.15 / 0.99, 1.07 / 1.14, 1.13 / 1.04; top-8, 64 x 4 x 7168, checksum 1.15 / 0.96.
+constexpr int64_t kSplitFewTokens = 512;    // and fewer than kSplitFewUnits 1 KiB chunks of rows
+constexpr int64_t kSplitFewUnits = 4096;
+constexpr int kSplitFlagChoices = 4;        // with more, Token-Flag Fusion is faster joined
+constexpr int64_t kSplitShortTokens = 4096;  // rows of one 1 KiB chunk, more than one batch per workgroup
+constexpr int kSplitShortSentinel = 8, kSplitShortMarks = 3;  // and at most this many choices
+inline int joined_form(const Geom& g, int H, int sync) {
+  if (g.k <= kFewChoices) return kFormFew;
+  const int cchunks = (H / 8 + kWave - 1) / kWave;
+  return sync == kDafNone && cchunks >= kWideChunks && g.T >= kWideTokens ? kFormWide : kFormGeneral;
+}
+inline int decomposed_form(const Geom& g, int H, int sync) {
+  const int64_t cchunks = (H / 8 + kWave - 1) / kWave;
+  if (sync != kDafNone) {
+    const bool few_tokens = g.T <= kSplitFewTokens && g.T * cchunks < kSplitFewUnits &&
+                            (sync != kDafFlag || g.k <= kSplitFlagChoices);
+    const bool short_rows = cchunks == 1 && g.T > kSplitShortTokens &&
+                            g.k <= (sync == kDafSentinel ? kSplitShortSentinel : kSplitShortMarks);
+    if (few_tokens || short_rows) return kFormSplit;
+  }
+  return joined_form(g, H, sync);
+}
+
 // Workgroups of the launch by role, and the device's co-resident capacity for it.
 struct DecomposedPlan {
+  int form;
   int grid, count_groups, send_groups, capacity;
   int senders;      // workgroups that send: send_groups, or the whole grid
   int batch;        // tokens a send workgroup takes at a time
@@ -191,16 +248,19 @@ struct DecomposedPlan {
 // per layer at 2 / 3 workgroups (4 waves each): 32 ranks x 64 tokens x 7168 columns 108 / 112, 64 x 128 x
 // 7168 407 / 412, 16 x 128 x 2048 44.9 / 45.0. The layer variants also combine with them, and gathers want
 // more waves: at 3 / 4 workgroups 32 x 64 x 7168 168 / 158, 64 x 128 x 7168 636 / 629.
-// With one or two choices a wave has little to write: all that fit, and beyond one batch each the count
+// With one or two choices a wave has little to write: more workgroups, and beyond one batch each the count
 // workgroups join when they have counted (top-1 of 1024 columns on 32 ranks, us per layer without and with:
-// 1024 tokens each, layout and dispatch 120 / 99; 256 tokens each, the sentinel layer 48.7 / 46.4).
-constexpr int kSendPerCu = 2, kSendPerCuLayer = 4;
+// 1024 tokens each, layout and dispatch 120 / 99; 256 tokens each, the sentinel layer 48.7 / 46.4). At 3 / 4 / 5 / 7 of
+// them, layout and dispatch, top-2 x 1024 tokens x 256 columns 83.4 / 80.6 / 81.0 / 84.5, top-1 x 1024 x 4096 277 / 280 /
+// 284 / 285; the Sentinel layer of top-1 x 1024 x 4096 at 4 / 5 / 6 296 / 290 / 336.
+constexpr int kSendPerCu = 2, kSendPerCuLayer = 4, kSendPerCuFew = 4, kSendPerCuFewLayer = 5;
 
-// The plan on a device of `cus` compute units that holds `capacity` workgroups of the kernel at once. A
-// grid beyond the capacity (a count_groups that leaves no room for send workgroups) is the caller's to
+// The plan on a device of `cus` compute units that holds `capacity` workgroups of the kernel's form at once.
+// A grid beyond the capacity (a count_groups that leaves no room for send workgroups) is the caller's to
 // refuse; sums that would not fit an int saturate, so that such a grid is never below the capacity.
-inline DecomposedPlan split_decomposed(const Geom& g, int H, int count_groups, int sync, int capacity, int cus) {
+inline DecomposedPlan split_decomposed(const Geom& g, int H, int count_groups, int sync, int form, int capacity, int cus) {
   DecomposedPlan plan;
+  plan.form = form;
   plan.capacity = capacity;
   // Default split: one count workgroup per layout chunk, at most a quarter of what the device
   // holds at once.
@@ -209,20 +269,30 @@ inline DecomposedPlan split_decomposed(const Geom& g, int H, int count_groups, i
   const int64_t cchunks = (H / 8 + kWave - 1) / kWave;
   // Send: batches of up to four tokens, all workgroups with as many batches as the next.
   const bool few = g.k <= kFewChoices;
-  const int most_per_cu = few ? 1 << 16 : sync == kDafNone ? kSendPerCu : kSendPerCuLayer;
-  const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(capacity - nc, (int64_t)most_per_cu * cus));
-  const int64_t room = groups + (few && g.T > groups * kSendBatch ? nc : 0);
+  const int most_per_cu = sync == kDafNone ? (few ? kSendPerCuFew : kSendPerCu) : few ? kSendPerCuFewLayer : kSendPerCuLayer;
+  int64_t groups = std::max<int64_t>(1, std::min<int64_t>(capacity - nc, (int64_t)most_per_cu * cus));
+  const int64_t room = groups + (few && form != kFormSplit && g.T > groups * kSendBatch ? nc : 0);
   const int64_t rounds = std::max<int64_t>(1, (g.T + room * kSendBatch - 1) / (room * kSendBatch));
   const int64_t even = (g.T + room * rounds - 1) / (room * rounds);
-  // More tokens per batch than that where a row is so short that a wave would load fewer than kSendAhead
+  // More tokens per batch than that where a row is so short that a wave would load fewer than four
   // units, and every wave should place a token, as long as each compute unit keeps a workgroup (128 tokens of
-  // 2048 columns: one per batch 26.6 us, four 46.1).
-  const int64_t full = (kSendAhead * kSendBatch + cchunks - 1) / cchunks;
-  const int64_t batch = std::min<int64_t>(kSendBatch, std::max(even, std::min(full, g.T / cus)));
-  plan.batch = (int)std::max<int64_t>(1, batch);
+  // 2048 columns: one per batch 26.6 us, four 46.1); with few choices, and for rows that leave waves of the workgroup
+  // idle, also when it does not: every workgroup's start and its count at the end cost as well (256 tokens top-1 of
+  // 2048 columns: one per batch 16.8 us, four 15.6).
+  const int64_t full = (4 * kSendBatch + cchunks - 1) / cchunks;
+  int64_t batch = std::max(even, std::min(full, few && sync == kDafNone ? full : g.T / cus));
+  batch = std::max<int64_t>(batch, kSendBatch / cchunks);
+  plan.batch = (int)std::max<int64_t>(1, std::min<int64_t>(kSendBatch, batch));
+  if (form == kFormSplit) groups = std::max<int64_t>(1, (capacity - nc) / 2);
   plan.send_groups = (int)std::max<int64_t>(1, std::min<int64_t>(groups, (g.T + plan.batch - 1) / plan.batch));
   plan.grid = (int)std::min<int64_t>(nc + plan.send_groups, INT_MAX);
   plan.senders = room > groups ? plan.grid : plan.send_groups;
+  if (form == kFormSplit) {  // the rest combine, a (token, chunk) per wave at a time
+    plan.senders = plan.send_groups;
+    const int64_t units = (g.T * cchunks + kLayoutWaves - 1) / kLayoutWaves;
+    const int64_t rest = std::max<int64_t>(1, std::min<int64_t>(capacity - nc - plan.send_groups, units));
+    plan.grid = (int)std::min<int64_t>(plan.grid + rest, INT_MAX);
+  }
   // Combine: as many chunks per task as leave every wave a task, in runs of even length.
   const int64_t waves = (int64_t)plan.grid * kLayoutWaves;
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>(cchunks, (g.T * cchunks + waves - 1) / waves));

@@ -3,9 +3,15 @@
 
 extern "C" {
 
+int decomposed_form(int R, int E, int k, int Tr, int H, int sync) {
+  return epl::decomposed_form(epl::make_geom(R, E, k, Tr), H, sync);
+}
+
 // out: grid, count_groups, send_groups, senders, batch, combine_run.
-void plan_decomposed(int R, int E, int k, int Tr, int H, int count_groups, int sync, int capacity, int cus, int* out) {
-  const epl::DecomposedPlan p = epl::split_decomposed(epl::make_geom(R, E, k, Tr), H, count_groups, sync, capacity, cus);
+void plan_decomposed(int R, int E, int k, int Tr, int H, int count_groups, int sync, int form, int capacity, int cus,
+                     int* out) {
+  const epl::DecomposedPlan p =
+      epl::split_decomposed(epl::make_geom(R, E, k, Tr), H, count_groups, sync, form, capacity, cus);
   const int v[] = {p.grid, p.count_groups, p.send_groups, p.senders, p.batch, p.combine_run};
   for (int i = 0; i < 6; ++i) out[i] = v[i];
 }

@@ -2,7 +2,8 @@
 outputs are copies, whole numbers and an fmaf chain of fixed order, so no tolerance): send batches of one
 to four tokens whose last is short, waves without a unit, a wave's units in one and in several groups of
 loads, one and several 1 KiB chunks per combine task with a short last task, and choices that fill one,
-or run past one, group of gathers."""
+or run past one, group of gathers; layers whose
+senders go on to combine and layers that have workgroups for it."""
 import pytest
 
 from paper_2607_06202_amd import epl
@@ -23,6 +24,9 @@ pytestmark = pytest.mark.gpu
     (8, 32, 16, 33, 2568, 5),    # two whole groups of gathers, six chunks, the last of one vector
     (8, 64, 3, 513, 3592, 6),    # 4,104 tokens of eight chunks: several chunks per task
     (5, 40, 25, 11, 7168, 7),    # 55 tokens of 14 chunks: four groups of loads per wave
+    (16, 64, 2, 400, 1032, 8),   # 6,400 tokens, two choices: two rounds of batches, three chunks
+    (8, 32, 1, 1500, 264, 9),    # 12,000 tokens, one choice, half a chunk: combined by workgroups of their own
+    (32, 64, 3, 64, 4104, 10),   # 2,048 tokens of nine chunks
 ])
 def test_units(path, R, E, k, Tr, H, seed):
     if path == "decomposed":

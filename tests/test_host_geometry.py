@@ -17,10 +17,15 @@ def geo(tmp_path_factory):
     return ctypes.CDLL(so)
 
 
-def plan(geo, R, E, k, Tr, H, count_groups=0, sync=0, capacity=1280, cus=256):
+GENERAL, FEW, WIDE, SPLIT = range(4)  # the forms of the one-launch kernel
+
+
+def plan(geo, R, E, k, Tr, H, count_groups=0, sync=0, form=None, capacity=1280, cus=256):
     out = (ctypes.c_int * 6)()
-    geo.plan_decomposed(R, E, k, Tr, H, count_groups, sync, capacity, cus, out)
-    return dict(zip(("grid", "count_groups", "send_groups", "senders", "batch", "combine_run"), out))
+    if form is None:
+        form = geo.decomposed_form(R, E, k, Tr, H, sync)
+    geo.plan_decomposed(R, E, k, Tr, H, count_groups, sync, form, capacity, cus, out)
+    return dict(zip(("grid", "count_groups", "send_groups", "senders", "batch", "combine_run"), out), form=form)
 
 
 @pytest.mark.parametrize("sync", [0, 1, 2, 3])
@@ -29,8 +34,47 @@ def plan(geo, R, E, k, Tr, H, count_groups=0, sync=0, capacity=1280, cus=256):
 def test_count_groups_beyond_the_device_give_a_grid_beyond_it(geo, sync, k, count_groups):
     """A launch whose workgroups wait for each other must not start unless all of them fit on the device at
     once: the caller compares grid with capacity, so the grid's sum must not wrap below it."""
-    p = plan(geo, 64, 256, k, 128, 7168, count_groups, sync)
-    assert p["count_groups"] == count_groups and p["grid"] > 1280
+    for form in (None, SPLIT) if sync else (None,):
+        p = plan(geo, 64, 256, k, 128, 7168, count_groups, sync, form)
+        assert p["count_groups"] == count_groups and p["grid"] > 1280
+
+
+@pytest.mark.parametrize("sync", [0, 1, 2, 3])
+def test_one_launch_plans(geo, sync):
+    """Every plan over a grid of shapes and splits: all workgroups fit on the device, a batch has a wave for
+    each token's placement, every send workgroup has a batch (one without would go on to combine without having
+    waited for the offsets), no combine task is empty, and the split form keeps a workgroup that combines."""
+    forms = set()
+    for R in (1, 4, 32, 64, 256):
+        for k in (1, 2, 3, 8, 32):
+            for Tr in (1, 2, 5, 16, 128, 300, 1024):
+                for H in (8, 256, 512, 520, 2048, 4992, 7168, 1 << 20):
+                    for count_groups, capacity in ((0, 1280), (0, 1792), (1, 1280), (7, 1536), (1000, 1280), (1278, 1280)):
+                        p = plan(geo, R, R * (256 // R), k, Tr, H, count_groups, sync, capacity=capacity)
+                        what = (R, k, Tr, H, count_groups, p)
+                        T, chunks = R * Tr, -(-H // 512)
+                        assert p["grid"] <= capacity and 1 <= p["batch"] <= 4, what
+                        assert 1 <= p["send_groups"] <= -(-T // p["batch"]), what
+                        assert 1 <= p["combine_run"] <= chunks, what
+                        n = p["count_groups"] + p["send_groups"]
+                        if p["form"] == SPLIT:
+                            assert sync and p["senders"] == p["send_groups"] and p["grid"] > n, what
+                        else:
+                            assert p["grid"] == n and p["senders"] in (p["send_groups"], p["grid"]), what
+                        forms.add(p["form"])
+    assert forms == ({FEW, GENERAL, WIDE} if sync == 0 else {FEW, GENERAL, SPLIT})
+
+
+@pytest.mark.parametrize("sync,R,k,Tr,H,form", [
+    (0, 64, 8, 128, 7168, WIDE), (0, 32, 8, 63, 7168, GENERAL), (0, 16, 8, 128, 2048, GENERAL), (0, 32, 2, 128, 7168, FEW),
+    (1, 16, 8, 128, 2048, GENERAL), (1, 64, 8, 128, 7168, GENERAL),
+    (1, 32, 1, 1024, 256, SPLIT), (1, 64, 8, 128, 256, SPLIT), (1, 64, 9, 128, 256, GENERAL), (1, 32, 1, 1024, 1024, FEW),
+    (3, 16, 3, 700, 512, SPLIT), (3, 16, 4, 700, 512, GENERAL), (2, 16, 1, 256, 512, FEW), (2, 16, 1, 257, 512, SPLIT),
+    (1, 4, 2, 128, 256, SPLIT), (1, 4, 2, 129, 256, FEW), (2, 16, 4, 2, 4992, SPLIT), (2, 8, 8, 16, 2048, GENERAL),
+    (3, 64, 8, 4, 7168, SPLIT), (3, 64, 8, 8, 7168, GENERAL)])
+def test_forms_of_the_one_launch_layers(geo, sync, R, k, Tr, H, form):
+    """Both sides of each bound of the rule."""
+    assert geo.decomposed_form(R, R * (256 // R), k, Tr, H, sync) == form
 
 
 @pytest.mark.parametrize("T,pieces", [
