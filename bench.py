@@ -781,7 +781,7 @@ def main():
     # The dispatch leg is one kernel: the plain dispatch kernel, or (epl_dispatch_rows with the
     # layout's finalize fused in) the fused row kernel, whose bytes include the placement metadata.
     launches = 1 if mode in ("decomposed",) + layer_modes else epl.layout_dispatch_launches(cfg) if mode == "fused" else None
-    row_fused = mode == "fused" and launches == 3
+    row_fused = mode == "fused" and launches == 3 and w.payload == "bf16"
     if mode == "decomposed" and dom == "dispatch":
         dom_bytes = nbytes["layout"] + nbytes["dispatch"]  # the one launch does the whole layout and dispatch
     elif mode in layer_modes:

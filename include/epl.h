@@ -150,10 +150,9 @@ epl_status epl_dispatch(const epl_config *cfg, const void *x, const epl_layout_b
                         float *recv_scale, int64_t recv_rows_cap, void *stream);
 
 /* Layout and dispatch in one call: the same outputs as epl_layout followed by epl_dispatch
- * (Kernel Decomposition: the rows are placed as the tokens are sent). Small layouts (T*k <= 16384 and
- * Tr*k <= 4096) take a single launch whose workgroups work out their own tokens' rows and send them;
- * layouts of at most 512 chunks and 256 experts take three (counts, placement, rows; for bf16 payloads the
- * row kernel also writes recv_src and recv_j); others the layout's three and the dispatch. Arguments
+ * (Kernel Decomposition: the rows are placed as the tokens are sent). It launches the kernels of its two
+ * phases below, or, for small layouts of few tokens, one kernel whose workgroups work out their own tokens'
+ * rows and send them; epl_layout_dispatch_launches says how many. Arguments
  * are those of the two calls, with the same meaning, alignment and capacity rules; every status those
  * calls can return is returned before any launch. Its outputs are those of epl_layout_counts followed by
  * epl_dispatch_rows with the same arguments; the workspace's contents afterwards are unspecified. */
@@ -163,10 +162,11 @@ epl_status epl_layout_dispatch(const epl_config *cfg, const int32_t *topk_idx, c
 
 /* The two phases of epl_layout_dispatch, for callers that put work between them or time them
  * apart (Kernel Decomposition: counts and prefix sums, then sending and reordering).
- * epl_layout_counts launches the layout kernels: counts and placement for bf16 payloads with at most 256
- * pairs per layout chunk and at most 256 experts, whose row kernel writes recv_src and recv_j, otherwise
- * the whole layout. On return (stream order) send_cnt, rank_cnt, tok_nranks and num_invalid are final;
- * the other fields of L are final only after epl_dispatch_rows. Statuses as epl_layout.
+ * epl_layout_counts launches the layout kernels: one for small layouts (T*k <= 16384 and Tr*k <= 4096);
+ * counts and placement for layouts of at most 512 chunks and 256 experts whose counts fit 16 bits (always up to
+ * 480 chunks), whose bf16 row kernel writes recv_src and recv_j; otherwise histogram, scan and finalize. On
+ * return (stream order) send_cnt, rank_cnt, tok_nranks and num_invalid are final; the other fields of L are
+ * final only after epl_dispatch_rows. Statuses as epl_layout.
  * epl_dispatch_rows launches exactly one kernel: the row kernel that goes with it, or the
  * plain dispatch kernel. It must follow epl_layout_counts on the same stream (or be ordered
  * after it) with the same cfg, topk_idx, L and workspace, none of them changed in between;
@@ -393,10 +393,10 @@ epl_status epl_debug_f32_to_bf16(const float *in, uint16_t *out, int64_t n, void
  * (histogram, scan, finalize). Returns -1 if cfg is invalid. Host-only, no HIP calls.        */
 int epl_layout_launches(const epl_config *cfg);
 
-/* Kernel launches of epl_layout_dispatch's two phases for cfg: 2 (one-launch layout, dispatch),
- * 3 (counts, placement, the row kernel that writes recv_src and recv_j) or 4 (three-launch layout,
- * dispatch). epl_layout_counts issues all but the last of them. epl_layout_dispatch issues no more than
- * these (see there). Returns -1 if cfg is invalid. Host-only, no HIP calls.                    */
+/* Number of kernel launches epl_layout_dispatch issues for cfg: 1 (layout and rows together), 2 (one-launch
+ * layout, rows), 3 (counts, placement, rows) or 4 (histogram, scan, finalize, rows). With 2 to 4,
+ * epl_layout_counts issues all but the last of them and epl_dispatch_rows the last; with 1 they issue one
+ * each. Returns -1 if cfg is invalid. Host-only, no HIP calls.                                 */
 int epl_layout_dispatch_launches(const epl_config *cfg);
 
 /* Static strings; never NULL. */

@@ -87,49 +87,39 @@ epl_status check_layout_dispatch(const epl_config* cfg, const int32_t* topk_idx,
   return EPL_OK;
 }
 
-bool rows_fused(const epl::Geom& g, const epl_config* cfg) {
-  return !epl::layout_single(g) && epl::fused_dispatch_ok(g, cfg->payload == EPL_PAYLOAD_FP8_E4M3) &&
-         epl::place_layout(g);
-}
+bool is_fp8(const epl_config* cfg) { return cfg->payload == EPL_PAYLOAD_FP8_E4M3; }
 
-// The layout: histogram and place for the fused geometries, whose row kernel writes recv_src and recv_j,
-// otherwise all of it.
+// The layout of epl_layout_dispatch where the rows are a launch of their own: one launch for small layouts,
+// two up to kPlaceMaxChunks chunks (recv_src and recv_j then belong to the bf16 row kernel), else three.
 hipError_t run_counts(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx,
                       const epl_layout_buffers* L, int32_t* ws, hipStream_t s) {
-  if (rows_fused(g, cfg)) return epl::launch_layout_place(g, topk_idx, ws, *L, false, s);
+  if (epl::small_layout(g)) return epl::launch_small_layout(g, topk_idx, *L, s);
+  if (epl::place_layout(g)) return epl::launch_layout_place(g, topk_idx, ws, *L, is_fp8(cfg), s);
   return epl::launch_layout(g, topk_idx, ws, L->send_cnt, L->rank_cnt, L->expert_off, L->rank_off, L->seg_off,
                             L->tok_nranks, L->pair_row, L->pair_rslot, L->recv_src, L->recv_j, L->num_invalid, s);
 }
 
-// One kernel: the fused row kernel, or the plain bf16 / fp8 dispatch kernel.
-hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const epl_layout_buffers* L, const void* x, void* recv, float* recv_scale, int64_t cap, hipStream_t s) {
-  if (rows_fused(g, cfg))
-    return epl::launch_fused_dispatch(x, L->pair_row, recv, L->recv_src, L->recv_j, g.T, cfg->topk, cfg->hidden,
-                                      pitch_of(cfg), cap, s);
-  if (cfg->payload == EPL_PAYLOAD_FP8_E4M3)
+// Its rows: the plain bf16 or fp8 dispatch kernel, or after the place kernel the fused one.
+hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const epl_layout_buffers* L, const void* x, void* recv,
+                    float* recv_scale, int64_t cap, hipStream_t s) {
+  if (is_fp8(cfg))
     return epl::launch_dispatch_fp8(x, L->pair_row, recv, recv_scale, g.T, cfg->topk, cfg->hidden, pitch_of(cfg),
                                     cap, s);
+  if (!epl::small_layout(g) && epl::place_layout(g))
+    return epl::launch_fused_dispatch(x, L->pair_row, recv, L->recv_src, L->recv_j, g.T, cfg->topk, cfg->hidden,
+                                      pitch_of(cfg), cap, s);
   return epl::launch_dispatch_bf16(x, L->pair_row, recv, g.T, cfg->topk, cfg->hidden, pitch_of(cfg), cap, s);
 }
 
-// Layout and dispatch: one launch for the geometries small_layout accepts, else the two phases.
+// Layout and dispatch: one launch for the layers small_dispatch accepts, else the two phases.
 hipError_t run_layout_dispatch(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx,
                                const epl_layout_buffers* L, int32_t* ws, const void* x, void* recv, float* recv_scale,
                                int64_t cap, hipStream_t s) {
-  const bool fp8 = cfg->payload == EPL_PAYLOAD_FP8_E4M3;
-  if (epl::small_dispatch(g, cfg->hidden, fp8))
-    return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap, fp8, s);
-  hipError_t e;
-  if (epl::small_layout(g) || !epl::place_layout(g)) {
-    if ((e = run_counts(g, cfg, topk_idx, L, ws, s)) != hipSuccess) return e;
-    return run_rows(g, cfg, L, x, recv, recv_scale, cap, s);
-  }
-  if ((e = epl::launch_layout_place(g, topk_idx, ws, *L, fp8, s)) != hipSuccess) return e;
-  if (fp8)
-    return epl::launch_dispatch_fp8(x, L->pair_row, recv, recv_scale, g.T, cfg->topk, cfg->hidden, pitch_of(cfg),
-                                    cap, s);
-  return epl::launch_fused_dispatch(x, L->pair_row, recv, L->recv_src, L->recv_j, g.T, cfg->topk, cfg->hidden,
-                                    pitch_of(cfg), cap, s);
+  if (epl::small_dispatch(g, cfg->hidden, is_fp8(cfg)))
+    return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap,
+                                             is_fp8(cfg), s);
+  const hipError_t e = run_counts(g, cfg, topk_idx, L, ws, s);
+  return e != hipSuccess ? e : run_rows(g, cfg, L, x, recv, recv_scale, cap, s);
 }
 
 }  // namespace
@@ -178,7 +168,8 @@ EPL_EXPORT epl_status epl_dispatch_rows(const epl_config* cfg, const int32_t* to
   const epl_status st =
       check_layout_dispatch(cfg, topk_idx, L, workspace, ws_bytes, x, recv, recv_scale, recv_rows_cap);
   if (st != EPL_OK) return st;
-  return from_hip(run_rows(make_geom(cfg), cfg, L, x, recv, recv_scale, recv_rows_cap, static_cast<hipStream_t>(stream)));
+  return from_hip(run_rows(make_geom(cfg), cfg, L, x, recv, recv_scale, recv_rows_cap,
+                           static_cast<hipStream_t>(stream)));
 }
 
 EPL_EXPORT epl_status epl_layout_dispatch(const epl_config* cfg, const int32_t* topk_idx, const epl_layout_buffers* L,
@@ -204,7 +195,7 @@ epl_status decomposed_args(const epl_config* cfg, const epl_decomposed_opts* opt
     if (opts->test_ready_target > 0) o.ready_target = opts->test_ready_target;
   }
   o.spin_ticks = spin_us * 100;  // the real-time clock runs at 100 MHz
-  if (cfg->payload != EPL_PAYLOAD_BF16 || !epl::fused_dispatch_ok(make_geom(cfg), false)) return EPL_ERR_UNSUPPORTED;
+  if (cfg->payload != EPL_PAYLOAD_BF16 || !epl::token_rows_ok(make_geom(cfg))) return EPL_ERR_UNSUPPORTED;
   *out = o;
   return EPL_OK;
 }
@@ -233,7 +224,7 @@ EPL_EXPORT epl_status epl_layout_dispatch_decomposed(const epl_config* cfg, cons
 
 EPL_EXPORT int epl_decomposed_plan(const epl_config* cfg, int32_t count_groups, int32_t* grid, int32_t* capacity) {
   if (check_config(cfg) != EPL_OK || count_groups < 0) return -1;
-  if (cfg->payload != EPL_PAYLOAD_BF16 || !epl::fused_dispatch_ok(make_geom(cfg), false)) return -1;
+  if (cfg->payload != EPL_PAYLOAD_BF16 || !epl::token_rows_ok(make_geom(cfg))) return -1;
   epl::DecomposedPlan plan;
   if (epl::plan_decomposed(make_geom(cfg), cfg->hidden, count_groups, epl::kDafNone, &plan) != hipSuccess) return -1;
   if (grid) *grid = plan.grid;
@@ -377,8 +368,7 @@ EPL_EXPORT epl_status epl_layout_dispatch_noalloc(const epl_config* cfg, const i
 EPL_EXPORT int epl_layout_dispatch_launches(const epl_config* cfg) {
   if (check_config(cfg) != EPL_OK) return -1;
   const epl::Geom g = make_geom(cfg);
-  if (epl::layout_single(g)) return 2;
-  return epl::fused_dispatch_ok(g, cfg->payload == EPL_PAYLOAD_FP8_E4M3) ? 3 : 4;
+  return epl::layout_dispatch_launches(g, cfg->hidden, is_fp8(cfg));
 }
 
 EPL_EXPORT epl_status epl_locate_rows(const epl_config* cfg, const int32_t* expert_off, const int32_t* rows,

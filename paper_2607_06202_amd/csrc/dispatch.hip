@@ -144,8 +144,8 @@ hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* r
   return hipGetLastError();
 }
 
-bool fused_dispatch_ok(const Geom& g, bool fp8) {
-  return !fp8 && g.CT * g.k <= kFusedSlots * kWave && g.E <= kFusedPer * kWave;
+bool token_rows_ok(const Geom& g) {
+  return g.CT * g.k <= kFusedSlots * kWave && g.E <= kFusedPer * kWave;
 }
 
 hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* recv, float* recv_scale, int64_t T,

@@ -258,10 +258,9 @@ hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* rec
 hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* recv, int32_t* recv_src,
                                  int32_t* recv_j, int64_t T, int k, int H, int pitch, int64_t cap,
                                  hipStream_t stream);
-// The geometries whose two phases are launch_layout_place and launch_fused_dispatch, and which the
-// decomposed launch takes.
-bool fused_dispatch_ok(const Geom& g, bool fp8);
-// The decomposed single-launch layout and dispatch (bf16, the geometries fused_dispatch_ok
+// The geometries whose tokens the decomposed launch can place one by one.
+bool token_rows_ok(const Geom& g);
+// The decomposed single-launch layout and dispatch (bf16, the geometries token_rows_ok
 // accepts). count_groups 0 picks the default split; spin_ticks bounds every wait (100 MHz ticks);
 // ready_target is the published value the send workgroups wait for (1; a test passes 2 to force a
 // give-up). wait_status receives 0, or the give-up bits, when the launch completes.

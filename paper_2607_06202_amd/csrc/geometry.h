@@ -143,6 +143,12 @@ inline bool place_layout(const Geom& g) {
   return g.E <= kPlaceExperts && g.nblk <= kPlaceMaxChunks && place_sum(place_geom(g)) < 65536;
 }
 
+// Kernels that epl_layout_dispatch launches: the layout with its rows, or the layout's launches and the rows'.
+inline int layout_dispatch_launches(const Geom& g, int H, bool fp8) {
+  if (small_dispatch(g, H, fp8)) return 1;
+  return small_layout(g) ? 2 : place_layout(g) ? 3 : 4;
+}
+
 // ------------------------------------------------------------------------ row kernels
 // Workgroups for `units` units, `per_group` to a workgroup of `threads` threads, of a kernel that strides
 // over its units. HIP takes fewer than 2^32 threads per grid dimension (gridDim * blockDim), which 1 KiB

@@ -848,9 +848,8 @@ def layout_launches(cfg: Config) -> int:
 
 
 def layout_dispatch_launches(cfg: Config) -> int:
-    """Kernel launches of layout_dispatch's two phases for cfg: 2, 3 or 4; layout_counts issues all but the
-    last. layout_dispatch itself issues no more than these: a single one where T*k <= 16384 and
-    Tr*k <= 4096, three for layouts of at most 512 chunks and 256 experts."""
+    """Kernel launches layout_dispatch issues for cfg: 1 (layout and rows together) to 4. layout_counts
+    issues all but the last of them; with a single one, layout_counts and dispatch_rows issue one each."""
     n = lib().epl_layout_dispatch_launches(ctypes.byref(cfg))
     if n < 0:
         raise EplError(1, "epl_layout_dispatch_launches")

@@ -43,7 +43,7 @@ def test_exports_every_declared_symbol(lib):
 
 
 def test_layout_launch_count():
-    """One launch up to T*k = 16384, Tr*k = 4096 and 64 KiB of LDS; three beyond."""
+    """One launch up to T*k = 16384, Tr*k = 4096 and 9*E + 6*R = 12287; three beyond."""
     for name, want in [("tiny", 1), ("decode_ep64", 3), ("prefill_ep32", 3), ("skewed_fp8_ep64", 3),
                        ("large_ep256", 3)]:
         w = W.WORKLOADS[name]
@@ -52,23 +52,25 @@ def test_layout_launch_count():
     assert epl.layout_launches(epl.config(32, 256, 8, 64, 65)) == 3      # T*k = 16640
     assert epl.layout_launches(epl.config(2, 16, 8, 64, 512)) == 1       # Tr*k = 4096
     assert epl.layout_launches(epl.config(2, 16, 8, 64, 513)) == 3       # Tr*k = 4104
-    assert epl.layout_launches(epl.config(64, 1024, 8, 64, 32)) == 1     # LDS 53.5 KiB
-    assert epl.layout_launches(epl.config(1024, 1024, 2, 64, 2)) == 3    # LDS 76 KiB
+    assert epl.layout_launches(epl.config(64, 1024, 8, 64, 32)) == 1     # 9*E + 6*R = 9600
+    assert epl.layout_launches(epl.config(1024, 1024, 2, 64, 2)) == 3    # 9*E + 6*R = 15360
     assert epl.layout_launches(epl.config(2, 16, 8, 64, 0)) == 1         # no tokens
     with pytest.raises(epl.EplError):
         epl.layout_launches(epl.config(3, 16, 8, 64, 4))                 # E % R != 0
 
 
 def test_layout_dispatch_launch_count():
-    """The finalize step runs inside the dispatch for bf16 with at most 256 pairs per chunk and 256
-    experts (3 launches); small layouts take 2, everything else 4."""
-    want = {"tiny": 2, "decode_ep64": 3, "prefill_ep32": 4, "skewed_fp8_ep64": 4, "large_ep256": 4}
+    """One launch for small layouts of few tokens, two for small layouts of many, three (counts, placement,
+    rows) up to 512 chunks and 256 experts, four beyond."""
+    want = {"tiny": 1, "decode_ep64": 3, "prefill_ep32": 4, "skewed_fp8_ep64": 3, "large_ep256": 3}
     for name, n in want.items():
         w = W.WORKLOADS[name]
         assert epl.layout_dispatch_launches(epl.config(w.R, w.E, w.k, w.H, w.Tr, w.payload)) == n, name
-    assert epl.layout_dispatch_launches(epl.config(64, 256, 8, 7168, 128, "fp8")) == 4  # decode shape, fp8
+    assert epl.layout_dispatch_launches(epl.config(4, 64, 1, 64, 4096)) == 2            # 4096 pairs per rank, top-1
+    assert epl.layout_dispatch_launches(epl.config(64, 256, 8, 7168, 128, "fp8")) == 3  # decode shape, fp8
     assert epl.layout_dispatch_launches(epl.config(64, 512, 8, 7168, 128)) == 4         # 512 experts
-    assert epl.layout_dispatch_launches(epl.config(64, 256, 8, 7168, 130)) == 4         # 264 pairs per chunk
+    assert epl.layout_dispatch_launches(epl.config(64, 256, 8, 7168, 130)) == 3         # 264 pairs per chunk
+    assert epl.layout_dispatch_launches(epl.config(1, 256, 8, 64, 61441)) == 4          # 481 chunks of 1024 pairs
     with pytest.raises(epl.EplError):
         epl.layout_dispatch_launches(epl.config(3, 16, 8, 64, 4))
 

@@ -87,7 +87,7 @@ def test_bench_layer_full_size_every_element(name):
     idx_d = torch.from_numpy(idx).to(dev)
     _bench_layer(cfg, idx_d, x_d, w_d, L, recv, scale, y_zero if fp8 else recv, out)
     torch.cuda.synchronize()
-    assert epl.layout_dispatch_launches(cfg) == {"decode_ep64": 3, "large_ep256": 4, "skewed_fp8_ep64": 4}[name]
+    assert epl.layout_dispatch_launches(cfg) == 3
 
     ref = oracle.layout(w.R, w.E, w.k, w.Tr, idx)
     P = ref.P

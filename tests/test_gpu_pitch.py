@@ -62,11 +62,11 @@ def _pitched_y(rows, H, pitch, seed, dev):
 
 # (R, E, k, Tr, H, pitch, seed, payload, launches of epl_layout_dispatch)
 CASES = [
-    (4, 16, 2, 128, 256, 320, 0, "bf16", 2),       # the one-launch layout
-    (64, 256, 8, 40, 1032, 1088, 1, "bf16", 3),    # the fused finalize; a ragged last column chunk
+    (4, 16, 2, 128, 256, 320, 0, "bf16", 1),       # layout and rows in one launch
+    (64, 256, 8, 40, 1032, 1088, 1, "bf16", 3),    # counts, placement, rows; a ragged last column chunk
     (32, 256, 8, 72, 7168, 7936, 2, "bf16", 3),    # the decode row size at the benchmark's pitch
     (8, 512, 4, 2048, 264, 320, 3, "bf16", 4),     # 512 experts: layout K1-K3, then the plain kernel
-    (16, 64, 4, 512, 1024, 1088, 4, "fp8", 4),     # fp8 rows of 1 KiB at a pitch of 1,088 bytes
+    (16, 64, 4, 512, 1024, 1088, 4, "fp8", 3),     # fp8 rows of 1 KiB at a pitch of 1,088 bytes
     (8, 32, 3, 300, 2048, 2048 + 512, 5, "fp8", 2),  # fp8 after the one-launch layout
 ]
 
