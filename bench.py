@@ -5,7 +5,8 @@ A step is one pass of the whole hot path over one synthetic batch: the routing l
 scatter (epl_layout_dispatch, or epl_layout then epl_dispatch with --separate), then the
 gather-reduce (epl_combine), with identity experts in between (combine reads the receive buffer).
 Steps that carry timing events issue epl_layout_dispatch as its two phases, epl_layout_counts then
-epl_dispatch_rows (the same kernels), so that the row kernel is timed on its own. All inputs are
+epl_dispatch_rows (the same kernels), so that the row kernel is timed on its own; small layers, whose
+layout and rows are one kernel, are issued as they are and that kernel is timed. All inputs are
 resident in HBM before timing starts. The token matrix x is read from byte-identical copies in
 turn, at least 512 MB in total, so that no step finds its input in the 256 MB memory-side cache.
 
@@ -94,8 +95,8 @@ def algorithmic_bytes(T, k, H, R, E, P, payload):
     combine = P * H * 2 + 2 * T * k * 4 + T * H * 2
     placement = 4 * ((E + 1) + (R + 1) + E * R + 2 * T * k + 2 * P)  # offsets, pair rows/slots, recv_src/j
     layout = T * k * 4 + 4 * (R * E + R * R + T + 1) + placement
-    # The row kernel with the layout's finalize step fused in also writes the placement metadata.
-    return {"layout": layout, "dispatch": dispatch, "combine": combine, "rows_fused": dispatch + placement,
+    # The row kernel that follows the placement kernel also writes recv_src and recv_j.
+    return {"layout": layout, "dispatch": dispatch, "combine": combine, "rows_fused": dispatch + 4 * 2 * P,
             "total": layout + dispatch + combine}
 
 
@@ -579,10 +580,13 @@ def main():
         marks = epl.alloc_marks(cfg, dev, recv.shape[0])
         variant = epl.DAF_TOKEN_FLAG_FUSION if mode == "flag" else epl.DAF_DATA_CHECKSUM
     status_d = torch.zeros(1, dtype=torch.int32, device=dev)
+    launches = (1 if mode in ("decomposed",) + layer_modes else
+                epl.layout_dispatch_launches(cfg) if mode == "fused" else None)
+    one_kernel = mode == "fused" and launches == 1  # epl_layout_dispatch has no phases to time apart
 
     def layout_dispatch(i, mark=None):
         """Layout and dispatch of step i. mark(), when given, runs between the layout's kernels and
-        the row kernel; the decomposed call is one launch, so there it runs before it."""
+        the row kernel; where both are one launch, it runs before it."""
         xi = xs[i % n_x]
         if mode == "sentinel":  # the whole layer, combine included, in one launch
             if mark is not None:
@@ -606,7 +610,9 @@ def main():
                 mark()
             epl.dispatch_scheduled(cfg, xi, L, args.scheduled, remap_rows=args.remap_rows, recv=recv,
                                    recv_scale=recv_scale)
-        elif mode == "fused" and mark is None:
+        elif mode == "fused" and (mark is None or one_kernel):
+            if mark is not None:
+                mark()
             epl.layout_dispatch(cfg, idx_d, xi, out=L, recv=recv, recv_scale=recv_scale)
         else:
             if mode == "fused":
@@ -622,7 +628,7 @@ def main():
 
     def step(i, ev=None):
         # With events the fused call is issued as its two phases (the same kernels), so the legs
-        # are epl_layout_counts and epl_dispatch_rows.
+        # are epl_layout_counts and epl_dispatch_rows; where it is one kernel, nothing and all of it.
         if ev is not None:
             ev[0].record(stream)
         layout_dispatch(i, None if ev is None else (lambda: ev[1].record(stream)))
@@ -689,9 +695,10 @@ def main():
             ev = dev_ev.get(i)
             if prep is not None:
                 if ev is not None and dom == "dispatch":
-                    prep.layout_counts()
+                    if not one_kernel:
+                        prep.layout_counts()
                     ev[0].record(stream)
-                    prep.dispatch_rows(i)
+                    (prep.layout_dispatch if one_kernel else prep.dispatch_rows)(i)
                     ev[1].record(stream)
                     prep.combine()
                     continue
@@ -763,7 +770,8 @@ def main():
         dom_us = float(np.mean(per[:, 1 if dom == "dispatch" else 2]))
 
     pct = lambda a: [round(float(v), 2) for v in np.percentile(a, [10, 50, 90])]
-    legs = {"decomposed": ("before_launch", "layout_dispatch_decomposed"), "fused": ("layout_counts", "dispatch_rows"),
+    legs = {"decomposed": ("before_launch", "layout_dispatch_decomposed"),
+            "fused": ("before_launch", "layout_dispatch") if one_kernel else ("layout_counts", "dispatch_rows"),
             "separate": ("layout", "dispatch"), "sentinel": ("before_launch", "layer_sentinel"),
             "flag": ("before_launch", "layer_data_as_flag"), "checksum": ("before_launch", "layer_data_as_flag"),
             "scheduled": ("layout", "dispatch_scheduled")}[mode]
@@ -778,11 +786,10 @@ def main():
     fabric_pairs = int(rc.sum() - np.trace(rc))
     row_bytes = w.H * 2 if w.payload == "bf16" else w.H + (w.H // 128) * 4
 
-    # The dispatch leg is one kernel: the plain dispatch kernel, or (epl_dispatch_rows with the
-    # layout's finalize fused in) the fused row kernel, whose bytes include the placement metadata.
-    launches = 1 if mode in ("decomposed",) + layer_modes else epl.layout_dispatch_launches(cfg) if mode == "fused" else None
+    # The dispatch leg is one kernel: the plain dispatch kernel, the fused row kernel after the placement
+    # kernel, which also writes recv_src and recv_j, or the small layers' kernel, which does the layout too.
     row_fused = mode == "fused" and launches == 3 and w.payload == "bf16"
-    if mode == "decomposed" and dom == "dispatch":
+    if (mode == "decomposed" or one_kernel) and dom == "dispatch":
         dom_bytes = nbytes["layout"] + nbytes["dispatch"]  # the one launch does the whole layout and dispatch
     elif mode in layer_modes:
         dom, dom_bytes = "dispatch", nbytes["total"]  # the one launch is the whole layer
@@ -791,6 +798,7 @@ def main():
     achieved = dom_bytes / (dom_us * 1e-6) / 1e9
     kname = {"dispatch": "decomposed_kernel" if mode in ("decomposed",) + layer_modes else
              "dispatch_scheduled_kernel" if mode == "scheduled" else
+             "route_single_kernel" if one_kernel else
              "fused_bf16_kernel" if row_fused else
              "dispatch_fp8_kernel" if w.payload == "fp8" else "dispatch_bf16_kernel",
              "combine": "combine_kernel"}[dom]

@@ -30,15 +30,15 @@ def test_decode_bytes_from_the_sizes_of_x_and_recv():
     assert abs(b["total"] / (0.7 * 8e12) * 1e6 - 377.9) < 0.05
 
 
-def test_fused_row_kernel_bytes_add_the_placement_metadata():
-    """The row kernel with the layout's finalize step fused in writes the expert, rank and segment
-    offsets, the pair rows and slots, and recv_src / recv_j on top of the dispatch's own bytes."""
+def test_fused_row_kernel_bytes_add_what_it_writes_of_the_layout():
+    """The row kernel that follows the placement kernel writes recv_src and recv_j on top of the dispatch's
+    own bytes; the expert, rank and segment offsets and the pair rows and slots are the placement kernel's."""
     b = _bytes("decode_ep64")
     R, E, T, k, P = 64, 256, 8192, 8, 65536
     placement = 4 * ((E + 1) + (R + 1) + E * R + 2 * T * k + 2 * P)
     assert placement == 1_115_400
-    assert b["rows_fused"] == b["dispatch"] + placement
-    assert placement < b["layout"]  # the layout still accounts for them once in the total
+    assert b["rows_fused"] == b["dispatch"] + 2 * P * 4
+    assert placement < b["layout"]  # the layout accounts for all of them once in the total
 
 
 def test_per_rank_payload_matches_the_papers_bandwidth_table():

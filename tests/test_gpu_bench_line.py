@@ -30,7 +30,9 @@ def test_bench_json_line():
     assert roof["bound"] == "hbm" and roof["peak"] == 8000.0 and roof["unit"] == "GB/s"
     assert roof["achieved"] > 0 and abs(roof["frac"] - roof["achieved"] / roof["peak"]) < 1e-3
     assert "traffic" in roof and "traffic_GBps" in roof
-    assert roof["kernel"] in ("combine_kernel", "dispatch_bf16_kernel", "fused_bf16_kernel")
+    assert roof["kernel"] in ("combine_kernel", "route_single_kernel")  # the kernels the timed steps launch
+    assert d["layout_dispatch_launches"] == 1 and set(d["per_call_us_p10_p50_p90"]) == {
+        "before_launch", "layout_dispatch", "combine", "layer"}
     cpu = d["cpu_baseline"]
     assert cpu["kind"] == "oracle" and cpu["cores"] >= 1 and cpu["value"] > 0 and cpu["sample"]
     assert cpu["bit_identical_to_single_thread"] is True
