@@ -1,9 +1,9 @@
 // Layout and dispatch in one launch, decomposed into count and send workgroups (the paper's
 // Kernel Decomposition, with its point-to-point synchronisation in place of global barriers).
 //
-// The three-launch path runs the layout's counts (K1), its CalCumSum scans (K2) and then the row
-// kernel that places and sends, with a kernel boundary between each. Here one launch holds both
-// roles, as the paper splits an NPU's vector cores into a group that counts tokens and computes
+// epl_layout_dispatch runs the layout's counts, its placement and then the row kernel (layout.hip,
+// dispatch.hip), with a kernel boundary between each. Here one launch holds both roles, with the bodies of
+// the three-launch layout's histogram (K1) and scan (K2), as the paper splits an NPU's vector cores into a group that counts tokens and computes
 // the prefix sums and a group that sends tokens:
 //   * count workgroups [0, nc) run K1 on chunks i, i + nc, ..., meet at a counter (every count
 //     workgroup has finished its chunks), run the K2 items i, i + nc, ..., and count themselves
@@ -11,7 +11,8 @@
 //     offsets (one slice each);
 //   * send workgroups [nc, grid) issue the loads of their first tokens, wait for the ready word,
 //     and then place and send batches of tokens, striding over them;
-//   * in the layer variants every workgroup then combines (Data-as-Flag, below).
+//   * in the layer variants every workgroup then combines (Data-as-Flag, below), or, in the split form, the
+//     workgroups past the senders combine meanwhile (geometry.h says which layers take which form).
 // The count/send split nc is the knob the paper sizes by its latency model (count cores in
 // proportion to the experts and inversely to the token load).
 //
@@ -157,7 +158,7 @@ __device__ __forceinline__ void count_role(const DecomposedArgs& A, int i, int32
   }
   // expert_off, rank_off and one slice of seg_off, from the published totals.
   if (workgroup_wait(&A.sync[kSyncReady], 1, A.spin_ticks, flag)) {
-    fused_meta_block<true>(A.F, i, A.nc, lds);
+    offsets_block(A.F, i, A.nc, lds);
   } else {
     if (threadIdx.x == 0) atomicOr(&A.sync[kSyncStatus], kGaveUpCount);
   }
@@ -289,7 +290,7 @@ __device__ __forceinline__ bool send_role(const DecomposedArgs& A, int j, int32_
       }
     }
     if (w < ntok) {
-      const int r = token_rows<false>(A.F, g0 + w, true, hist, lane);
+      const int r = token_rows(A.F, g0 + w, true, hist, lane);
       if (lane < k) rows_lds[w * k + lane] = r;
     }
     __syncthreads();
@@ -370,7 +371,7 @@ __device__ __forceinline__ void combine_role(const DecomposedArgs& A, int ci, in
     const int c0 = (int)(u - g * runs) * A.crun;
     const int c1 = min(c0 + A.crun, A.cchunks);
     const int wbits = __builtin_bit_cast(int, A.topk_w[g * k + min(lane, k - 1)]);
-    const int rows = token_rows<false>(A.F, g, false, hist, lane);
+    const int rows = token_rows(A.F, g, false, hist, lane);
     int c = c0;
     for (; c < c1; ++c) {
       const int v = c * kWave + lane;
@@ -495,7 +496,7 @@ __device__ __forceinline__ void combine_rows(const DecomposedArgs& A, int ci, in
   for (int64_t u = (int64_t)ci * kWavesPerBlock + w; u < units; u += stride) {
     const int64_t g = u / A.cchunks;
     const int c = (int)(u - g * A.cchunks);
-    const int rows = token_rows<false>(A.F, g, false, hist, lane);
+    const int rows = token_rows(A.F, g, false, hist, lane);
     const int v = c * kWave + lane;
     const bool on = v < nv;
     const int vl = min(v, nv - 1);

@@ -72,9 +72,9 @@ inline Geom make_geom(int R, int E, int k, int Tr) {
 // 29.2 / 32.1.
 constexpr int64_t kSingleMaxPairs = 16384;     // T*k
 constexpr int64_t kSingleMaxRankPairs = 4096;  // Tr*k
-// Bound on 9 E + 6 R for epl_layout alone, whose launch count (epl_layout_launches) it is part of.
-// epl_layout_dispatch has no such bound: 4K pairs on 1024 ranks of one expert take 26.6 us per layer in
-// one launch, 51.9 in three.
+// Bound on 9 E + 6 R for epl_layout alone, whose launch count (epl_layout_launches) it is part of; the kernel
+// needs none. epl_layout_dispatch and its phases have no such bound: 4K pairs on 1024 ranks of one expert take 26.6 us
+// per layer in one launch, 51.9 with a three-launch layout.
 constexpr int64_t kSingleMaxTable = 12287;
 
 inline bool small_layout(const Geom& g) {

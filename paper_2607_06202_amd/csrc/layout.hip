@@ -21,8 +21,8 @@
 //                      its stable rank among equal keys: ballot match over the key bits,
 //                      popcount of the lanes below, per-wave LDS running counts. A cross-wave
 //                      prefix then yields pair_row, recv_src, recv_j and pair_rslot.
-// For layouts of at most kPlaceMaxChunks chunks and 256 experts epl_layout_dispatch takes two launches
-// before the rows, route_count and route_place.
+// For layouts of at most kPlaceMaxChunks chunks and 256 experts (place_layout) epl_layout_dispatch takes two
+// launches before the rows, route_count and route_place.
 //
 // Small integer quotients (pair -> token within a chunk, expert -> rank, seg_off index -> expert;
 // every numerator < 2^21) use small_div, which is exact in that range.

@@ -1,7 +1,7 @@
 // Device bodies of the row kernels: the units the dispatch kernels send (dispatch.hip, small.hip,
-// schedule.hip), and the placement of a token's pairs from the decomposed single launch's counts
-// (decomposed.hip), which reads the layout data other workgroups of the same kernel wrote with
-// device-scope loads (the C template argument, see ld32).
+// schedule.hip), and what the decomposed single launch (decomposed.hip) works out from its counts: the
+// placement of a token's pairs, with plain loads after an acquire of what count workgroups published, and
+// the offsets, with device-scope loads of what other count workgroups wrote (see ld32).
 #pragma once
 
 #include "epl_internal.h"
@@ -125,7 +125,6 @@ struct FusedLayout {
 // kFusedPer * 64 experts. hist is this wave's LDS [E + R].
 constexpr int kFusedSlots = 4;
 constexpr int kFusedPer = 4;
-template <bool C>
 __device__ __forceinline__ int token_rows(const FusedLayout& F, int64_t g, bool meta, int32_t* hist, int lane) {
   const Geom& G = F.G;
   const int k = G.k;
@@ -140,24 +139,24 @@ __device__ __forceinline__ int token_rows(const FusedLayout& F, int64_t g, bool 
   // Every independent load first (indices clamped, so none sits behind a branch).
   const bool mine = lane < k;
   const int e = F.idx[g * k + min(lane, k - 1)];
-  const uint32_t fm = ld32<C>(&F.fmask[g]);
+  const uint32_t fm = F.fmask[g];
   const int per = (G.E + kWave - 1) / kWave;  // experts per lane in the prefix of recv_cnt, <= kFusedPer
   int rc[kFusedPer];
 #pragma unroll
-  for (int i = 0; i < kFusedPer; ++i) rc[i] = ld32<C>(&F.recv_cnt[min(lane * per + i, G.E - 1)]);
+  for (int i = 0; i < kFusedPer; ++i) rc[i] = F.recv_cnt[min(lane * per + i, G.E - 1)];
   int ep[kFusedSlots];
   uint32_t fp[kFusedSlots];
 #pragma unroll
   for (int q = 0; q < kFusedSlots; ++q) {
     const int i = min(q * kWave + lane, max(nb - 1, 0));
     ep[q] = nb > 0 ? F.idx[cb + i] : -1;
-    fp[q] = nb > 0 ? ld32<C>(&F.fmask[tok0 + small_div(i, G.inv_k)]) : 0u;
+    fp[q] = nb > 0 ? F.fmask[tok0 + small_div(i, G.inv_k)] : 0u;
   }
   const bool valid = mine && (unsigned)e < (unsigned)G.E;
   const int ev = valid ? e : 0;
   const int d = valid ? small_div(e, G.inv_El) : 0;
-  const int base_e = ld32<C>(&F.chunk_e[(int64_t)ev * G.nblk + b]);
-  const int base_r = ld32<C>(&F.chunk_r[(int64_t)b * G.R + d]);
+  const int base_e = F.chunk_e[(int64_t)ev * G.nblk + b];
+  const int base_r = F.chunk_r[(int64_t)b * G.R + d];
 
   // Histograms of the chunk's earlier pairs: experts, and ranks of first pairs.
   int32_t* he = hist;
@@ -214,10 +213,9 @@ __device__ __forceinline__ int token_rows(const FusedLayout& F, int64_t g, bool 
   return mine ? row : -1;
 }
 
-// Workgroups past the dispatch units: expert_off and rank_off (the first of them) and one slice
-// of seg_off each. lds holds at least E + 1 ints.
-template <bool C>
-__device__ __forceinline__ void fused_meta_block(const FusedLayout& F, int m, int nmeta, int32_t* lds) {
+// Count workgroup m of nmeta: expert_off and rank_off (the first of them) and one slice of seg_off each. lds holds
+// at least E + 1 ints.
+__device__ __forceinline__ void offsets_block(const FusedLayout& F, int m, int nmeta, int32_t* lds) {
   static_assert(kDispatchThreads == kLayoutThreads, "block_exclusive_sum assumes layout-sized workgroups");
   __shared__ int32_t scratch[kLayoutWaves];
   const Geom& G = F.G;
@@ -227,7 +225,7 @@ __device__ __forceinline__ void fused_meta_block(const FusedLayout& F, int m, in
   const int e0 = min(G.E, tid * per), e1 = min(G.E, e0 + per);
   int rc[kLayoutSlots];
 #pragma unroll
-  for (int q = 0; q < kLayoutSlots; ++q) rc[q] = ld32<C>(&F.recv_cnt[min(e0 + q, G.E - 1)]);
+  for (int q = 0; q < kLayoutSlots; ++q) rc[q] = ld32<true>(&F.recv_cnt[min(e0 + q, G.E - 1)]);
   int sum = 0;
 #pragma unroll
   for (int q = 0; q < kLayoutSlots; ++q) sum += e0 + q < e1 ? rc[q] : 0;
@@ -249,7 +247,7 @@ __device__ __forceinline__ void fused_meta_block(const FusedLayout& F, int m, in
   const int seg_per = (nseg + nmeta - 1) / nmeta;
   const int i1 = min(nseg, (m + 1) * seg_per);
   for (int i = m * seg_per + tid; i < i1; i += kLayoutThreads)
-    F.seg_off[i] = eoff[small_div(i, G.inv_R)] + ld32<C>(&F.seg_rel[i]);
+    F.seg_off[i] = eoff[small_div(i, G.inv_R)] + ld32<true>(&F.seg_rel[i]);
 }
 
 }  // namespace epl

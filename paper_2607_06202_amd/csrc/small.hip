@@ -21,7 +21,7 @@
 // each token's choices one after another in LDS, followed by the dispatch kernel: 1K pairs on 4 ranks
 // 12.2 -> 8.8 us, 1K pairs on 16 ranks 16.7 -> 9.2 us, 16K pairs of 2048 columns 40.2 -> 35.4 us;
 // 4.7K pairs of 5120 columns through the plain calls 47.4 -> 41.5 us. With the same layout but the
-// dispatch as a second launch these take 12.9, 12.9, 38.7 and 44.0 us.
+// dispatch as a second launch these take 12.9, 12.9, 38.7 and 44.0 us; small_dispatch says which layers do.
 #include "rows_body.h"
 
 namespace epl {

@@ -362,14 +362,14 @@ int main() {
   hipStream_t stream;
   HIP_OK(hipStreamCreate(&stream));
   const Case cases[] = {
-      {8, 32, 4, 50, 1024, EPL_PAYLOAD_BF16},     // one-launch layout
-      {4, 16, 8, 100, 512, EPL_PAYLOAD_FP8_E4M3},  // fp8, one-launch layout
-      {32, 256, 8, 80, 256, EPL_PAYLOAD_BF16},    // T*k = 20480: three-launch layout
-      {64, 256, 8, 40, 1024, EPL_PAYLOAD_BF16},   // finalize fused into the row kernel
+      {8, 32, 4, 50, 1024, EPL_PAYLOAD_BF16},     // layout and rows in one launch
+      {4, 16, 8, 100, 512, EPL_PAYLOAD_FP8_E4M3},  // the same, fp8
+      {32, 256, 8, 80, 256, EPL_PAYLOAD_BF16},    // T*k = 20480: counts, placement, rows
+      {64, 256, 8, 40, 1024, EPL_PAYLOAD_BF16},   // the same, longer rows
       {2, 8, 3, 0, 64, EPL_PAYLOAD_BF16},         // no tokens
-      {64, 256, 8, 40, 1024, EPL_PAYLOAD_BF16, 1024 + 768},  // fused, rows 1.5 KiB apart beyond their 2 KiB
+      {64, 256, 8, 40, 1024, EPL_PAYLOAD_BF16, 1024 + 768},  // rows 1.5 KiB apart beyond their 2 KiB
       {4, 16, 8, 100, 512, EPL_PAYLOAD_FP8_E4M3, 576},       // fp8 rows 64 bytes apart beyond their 512
-      {32, 256, 8, 80, 256, EPL_PAYLOAD_BF16, 320},          // three-launch layout, padded rows
+      {32, 256, 8, 80, 256, EPL_PAYLOAD_BF16, 320},          // padded rows
   };
   bool ok = true;
   uint64_t seed = 12345;

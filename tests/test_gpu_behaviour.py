@@ -33,7 +33,7 @@ def _inputs(R, E, k, Tr, H, seed, dev):
 
 @pytest.mark.parametrize("R,E,k,Tr,H,calls", [
     (16, 64, 8, 24, 1024, "separate"),   # one-launch layout, then dispatch, combine
-    (64, 256, 8, 40, 1024, "fused"),     # counts, fused row kernel, combine, row location
+    (64, 256, 8, 40, 1024, "fused"),     # counts, placement, rows, combine, row location
     (16, 512, 8, 256, 512, "phases"),    # three-launch layout then dispatch, as epl_layout_counts + epl_dispatch_rows
 ])
 def test_graph_capture_replays_match_eager(R, E, k, Tr, H, calls):

@@ -1,7 +1,6 @@
 """Full-size parity on the benchmark's own call path, element by element.
 
-The benchmark's layer is epl_layout_dispatch (the layout's counts, then the row kernel, with the
-finalize step fused in where it applies) into a receive buffer allocated as one physically
+The benchmark's layer is epl_layout_dispatch (the layout's kernels, then the row kernel) into a receive buffer allocated as one physically
 contiguous block at the benchmark's row pitch, then epl_combine reading that buffer (identity
 experts). These tests run
 exactly that sequence, at the named workloads' full sizes, after a first layer with other
@@ -13,7 +12,7 @@ routing has left its data in every buffer, and compare with the CPU oracle:
   in parallel), on the identity rows and on independent expert rows.
 Prefill (15 GB of receive rows) is compared the same way, streamed in token chunks.
 
-Also: the fused row kernel with all four of its pair slots in use (256 pairs per chunk) against
+Also: the placement kernel's short form with all its steps in use (256 pairs per chunk) against
 the oracle directly, and the layout of every named workload at seeds 0-9.
 """
 import numpy as np
@@ -160,8 +159,8 @@ def test_bench_layer_prefill_streamed():
 
 @pytest.mark.parametrize("R,Tr,H,seed", [(32, 256, 264, 0), (64, 128, 8, 1), (16, 512, 1032, 2)])
 def test_fused_row_kernel_with_every_pair_slot_in_use(R, Tr, H, seed):
-    """8,192 tokens of top-8 give chunks of 32 tokens, 256 pairs: the fused row kernel's four
-    64-pair slots are all in use, as in the decode layer. Layout and every payload row against the
+    """8,192 tokens of top-8 give chunks of 32 tokens, 256 pairs, the most that the placement kernel's form of
+    two steps per wave takes, as in the decode layer. Layout and every payload row against the
     oracle, with invalid ids and duplicates among the choices."""
     dev = device()
     E, k = 256, 8

@@ -1,12 +1,11 @@
 """epl_layout_dispatch, and its two phases epl_layout_counts + epl_dispatch_rows, against the CPU
-oracle: every layout output and the bf16 / fp8 payload, bit for bit. It takes three paths, and every
-case asserts which one it exercises:
-* 3 launches, the layout's finalize step fused into the bf16 dispatch (at most 256 pairs per
-  chunk and 256 experts): ragged last chunks, duplicates, invalid ids, 1 and 2 experts per rank,
-  more choices than experts, rows of 1, 2, 4 (ragged) and 5 column chunks, so that a
-  workgroup's waves cover four, two, one or parts of two tokens;
-* 4 launches, the layout then the dispatch (larger chunks, more experts, fp8);
-* 2 launches for small layouts."""
+oracle: every layout output and the bf16 / fp8 payload, bit for bit. Every case asserts how many launches
+the call takes:
+* 3, counts and placement and then the rows, of which the bf16 kernel also writes recv_src and recv_j:
+  ragged last chunks, duplicates, invalid ids, 1 and 2 experts per rank, more choices than experts, rows of
+  one to twenty 1 KiB chunks, ragged ones, so that a workgroup's two waves take one token or two;
+* 4, the three-launch layout then the dispatch (more experts or chunks);
+* 1 for a small layout, whose phases are one launch each."""
 import numpy as np
 import pytest
 import torch
@@ -61,9 +60,9 @@ def _check(R, E, k, Tr, H, payload, seed, idx=None, phases=False):
     (256, 256, 8, 64, 1032, 11, 3),  # the EP=256 chunking: 512 pairs per chunk, ragged last column chunk
     (4, 1024, 32, 300, 1032, 12, 4), # 1024 pairs per chunk, 1024 experts, ragged chunks
     (1024, 1024, 2, 40, 64, 13, 4),  # 1024 ranks of one expert
-    (64, 256, 8, 40, 4096, 8, 3),    # 2 column chunks per row: 2 tokens per workgroup
-    (32, 256, 8, 130, 6152, 9, 3),   # 4 chunks, the last one ragged (769 vectors per row)
-    (64, 256, 8, 40, 10240, 10, 3),  # 5 chunks: a workgroup's waves straddle two tokens
+    (64, 256, 8, 40, 4096, 8, 3),    # 8 column chunks per row
+    (32, 256, 8, 130, 6152, 9, 3),   # 13 chunks, the last one of one vector: workgroups straddle two tokens
+    (64, 256, 8, 40, 10240, 10, 3),  # 20 chunks
 ])
 @pytest.mark.parametrize("phases", [False, True])
 def test_layout_dispatch_bf16(R, E, k, Tr, H, seed, launches, phases):
@@ -126,7 +125,7 @@ def test_layout_dispatch_matches_separate_calls_at_full_size(name):
 @pytest.mark.parametrize("seed", range(12))
 def test_layout_dispatch_random_shapes(seed):
     """Random shapes through epl_layout_dispatch and its two phases (alternating by seed):
-    ranks, experts per rank, k, tokens per rank, hidden sizes of 1 to 5 column chunks with ragged
+    ranks, experts per rank, k, tokens per rank, hidden sizes of 1 to 19 1 KiB chunks with ragged
     tails, bf16 or fp8, with duplicates and invalid ids; every path the call can take appears."""
     rng = np.random.default_rng(1300 + seed)
     R = int(rng.choice([1, 4, 16, 32, 64, 128]))
@@ -145,17 +144,15 @@ def test_layout_dispatch_random_shapes(seed):
     _check(R, E, k, Tr, H, payload, seed, idx=idx, phases=bool(seed % 3 == 1))
 
 
-
-def test_fused_row_kernel_with_buffer_loads():
-    """An x of 200 MB or more is read through buffer loads, in the fused row kernel as in the
-    plain dispatch: 64 ranks of 100 tokens at H = 16,384 (210 MB of x, chunks of 25 tokens, so the
-    finalize step is still fused). The layout against the oracle; every packed row against its
+def test_row_kernel_after_placement_with_long_rows():
+    """Rows of 32 1 KiB chunks after the placement kernel (64 ranks of 100 tokens at H = 16,384), of which only a
+    token's first writes recv_src and recv_j. The layout against the oracle; every packed row against its
     source row, bit for bit."""
     dev = device()
     R, E, k, Tr, H = 64, 256, 8, 100, 16384
     T = R * Tr
     cfg = epl.config(R, E, k, H, Tr)
-    assert T * H * 2 >= 200 << 20 and epl.layout_dispatch_launches(cfg) == 3
+    assert epl.layout_dispatch_launches(cfg) == 3
     idx = W.distinct_uniform(21, np.arange(T), k, E).astype(np.int32)
     idx[::37, 2] = -1
     x_d = W.device_normal_bf16((T, H), seed=21, device=dev)
@@ -167,17 +164,19 @@ def test_fused_row_kernel_with_buffer_loads():
             L, recv, _ = epl.layout_dispatch(cfg, torch.from_numpy(idx).to(dev), x_d)
         torch.cuda.synchronize()
         ref = oracle.layout(R, E, k, Tr, idx)
-        assert_layout_equal(L, ref, "fused, buffer loads, phases=%s" % phases)
+        assert_layout_equal(L, ref, "long rows, phases=%s" % phases)
         src = torch.from_numpy(ref.recv_src.astype(np.int64)).to(dev)
         assert torch.equal(recv[:ref.P].view(torch.int16), x_d[src].view(torch.int16))
         del L, recv
 
 
 @pytest.mark.parametrize("R,E,k,Tr,H,seed,payload", [
-    (64, 256, 8, 40, 1024, 20, "bf16"),   # finalize fused into the row kernel
-    (4, 16, 2, 128, 256, 21, "bf16"),     # one-launch layout
-    (16, 64, 8, 300, 1032, 22, "bf16"),   # three-launch layout, then the plain dispatch
-    (16, 64, 8, 40, 1152, 23, "fp8"),     # fp8: three-launch layout, then the fp8 dispatch
+    (64, 256, 8, 40, 1024, 20, "bf16"),   # counts, placement, rows
+    (4, 16, 2, 128, 256, 21, "bf16"),     # layout and rows in one launch
+    (16, 64, 8, 300, 1032, 22, "bf16"),   # counts, placement, rows; ragged rows
+    (16, 512, 8, 300, 1032, 24, "bf16"),  # three-launch layout, then the plain dispatch
+    (16, 64, 8, 40, 1152, 23, "fp8"),     # fp8, layout and rows in one launch
+    (16, 64, 8, 300, 1152, 25, "fp8"),    # fp8: counts, placement, rows
 ])
 def test_prepared_layer_matches_the_plain_calls(R, E, k, Tr, H, seed, payload):
     """PreparedLayer (arguments checked and converted once) issues the same calls as

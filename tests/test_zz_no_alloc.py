@@ -47,8 +47,8 @@ def _compare(cfg, idx, x, dev, what):
 def test_noalloc_matches_workspace_call_on_shrinking_inputs():
     dev = device()
     cases = [
-        ("decode", 64, 256, 8, 128, 7168, "bf16", 0),   # fused finalize path, 0.41 MiB of scratch
-        ("random", 16, 64, 8, 1024, 1152, "fp8", 1),    # four launches, fp8; smaller
+        ("decode", 64, 256, 8, 128, 7168, "bf16", 0),   # counts, placement, rows; 0.41 MiB of scratch
+        ("random", 16, 64, 8, 1024, 1152, "fp8", 1),    # the same with fp8 rows; smaller
         ("random", 8, 32, 5, 300, 264, "bf16", 2),      # smaller again, ragged chunks, invalid ids
         ("tiny", 4, 16, 2, 128, 256, "bf16", 3),        # one-launch layout (scratch unused)
     ]
@@ -82,7 +82,7 @@ def test_noalloc_refuses_a_workspace_beyond_the_static_array():
 
 
 @pytest.mark.parametrize("R,E,k,Tr,H,pitch", [
-    (64, 256, 8, 40, 1032, 1088),  # finalize fused into the row kernel, rows a pitch apart
+    (64, 256, 8, 40, 1032, 1088),  # counts, placement, rows a pitch apart
     (8, 512, 4, 512, 264, 0),      # 512 experts: layout K1-K3, then the plain row kernel
 ])
 def test_noalloc_under_graph_capture(R, E, k, Tr, H, pitch):
