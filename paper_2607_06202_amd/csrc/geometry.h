@@ -85,6 +85,24 @@ inline bool layout_single(const Geom& g) {  // true if epl_layout runs as one la
   return small_layout(g) && 9 * (int64_t)g.E + 6 * g.R <= kSingleMaxTable;
 }
 
+// Tokens per group. Every group repeats the pass over all ids, so fewer groups are cheaper; but a
+// group also sends its tokens' rows with four waves only, so more groups hide more latency.
+// * Layout alone: 256 groups, one per compute unit, at most a wave of pairs each (layout of 16K
+//   pairs and dispatch and combine of 2048-wide rows, us for 256 / 512 / 1024 / 2048 groups: 38.2 /
+//   39.4 / 43.1 / 48.8).
+// * With the send: one 4 KiB piece (an fp8 pass) per wave, as long as the groups' passes stay under
+//   kSmallMaxCounts ids in all. Whole layer, us for 256 / 512 / 1024 / 2048 groups: 4.7K pairs of
+//   5120 columns 49.3 / 46.6 / 45.2 / 41.9; 8K pairs of 7168 57.3 / 56.3 / 55.6 / 55.6; 16K of 7168
+//   109.0 / 108.3 / 105.9 / 105.9; 16K of 2048 35.5 / 36.0 / 37.1 / 41.8; 16K (top-1) of 1024 44.2 /
+//   41.3 / 42.9 / 50.5.
+constexpr int64_t kSmallMaxCounts = 1 << 24;
+inline int group_tokens(const Geom& g, int pieces) {
+  const int64_t most = std::min<int64_t>(kWave / g.k, (g.T + 255) / 256);
+  const int64_t want = pieces ? std::max<int64_t>(kLayoutWaves / pieces, (g.T * g.T * g.k + kSmallMaxCounts - 1) / kSmallMaxCounts)
+                              : most;
+  return (int)std::max<int64_t>(1, std::min(want, most));
+}
+
 // Whether epl_layout_dispatch takes one launch for the layout and its rows (small.hip), or the rows a second
 // one. Every group of tokens counts all ids again and then sends with four waves, so many tokens are better
 // sent by the row kernel. Layout, dispatch and combine, speed in one launch / in two against a layout whose
@@ -95,13 +113,19 @@ inline bool layout_single(const Geom& g) {  // true if epl_layout runs as one la
 // quantising: top-2 on 4 ranks, 1536 tokens of 3072 columns 1.10 / 1.09, 2048 tokens 0.96 / 1.09; top-6,
 // 1536 x 3072 0.97 / 1.05; top-4, 2048 x 4096 0.93 / 1.02; top-8, 1536 x 7168 1.07 / 1.03.
 constexpr int64_t kSmallSendTokens = 2816;
+constexpr int64_t kSmallSendTokens1 = 4096;    // top-1, from four ranks on
 constexpr int64_t kSmallSendCounts = 1 << 25;  // T*T*k
-constexpr int64_t kSmallSendPasses = 3072;     // fp8, rows of fewer passes than a group has waves: tokens * passes
-constexpr int64_t kSmallSendWide = 1536;       // fp8, wider rows: tokens
+constexpr int64_t kSmallSendPasses = 4096, kSmallSendPassesMany = 3072;  // fp8, tokens * passes up to / beyond top-4
+constexpr int64_t kSmallSendWide = 1536;       // fp8, rows of as many passes as a group has waves, or more: tokens
+inline int small_pieces(int H, bool fp8) { return fp8 ? (H + 1023) / 1024 : (H + 2047) / 2048; }  // of a row: passes, or 4 KiB
 inline bool small_dispatch(const Geom& g, int H, bool fp8) {
-  if (!small_layout(g) || g.T > kSmallSendTokens || g.T * g.T * g.k > kSmallSendCounts) return false;
-  const int passes = (H + 1023) / 1024;
-  return !fp8 || g.T <= (passes < kLayoutWaves ? kSmallSendPasses / passes : kSmallSendWide);
+  if (!small_layout(g)) return false;
+  const int pieces = small_pieces(H, fp8);
+  // Ranks so short that the layout alone would take as many groups: sending with them costs no counting
+  // (1024 ranks of 16 tokens, top-1 x 512 columns: 42.0 us in one launch, 45.8 in two).
+  if (g.Tr <= group_tokens(g, pieces)) return true;
+  if (g.T > (g.k == 1 && g.R >= 4 ? kSmallSendTokens1 : kSmallSendTokens) || g.T * g.T * g.k > kSmallSendCounts) return false;
+  return !fp8 || g.T <= (pieces >= kLayoutWaves ? kSmallSendWide : (g.k <= 4 ? kSmallSendPasses : kSmallSendPassesMany) / pieces);
 }
 
 // ------------------------------------------------------------------------ layouts in two launches

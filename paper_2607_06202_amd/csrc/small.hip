@@ -252,26 +252,9 @@ __global__ void __launch_bounds__(kLayoutThreads) route_single_kernel(SmallArgs 
 }
 
 // ------------------------------------------------------------------------------------ host
-// Tokens per group. Every group repeats the pass over all ids, so fewer groups are cheaper; but a
-// group also sends its tokens' rows with four waves only, so more groups hide more latency.
-// * Layout alone: 256 groups, one per compute unit, at most a wave of pairs each (layout of 16K
-//   pairs and dispatch and combine of 2048-wide rows, us for 256 / 512 / 1024 / 2048 groups: 38.2 /
-//   39.4 / 43.1 / 48.8).
-// * With the send: one 4 KiB piece (an fp8 pass) per wave, as long as the groups' passes stay under
-//   kSmallMaxCounts ids in all. Whole layer, us for 256 / 512 / 1024 / 2048 groups: 4.7K pairs of
-//   5120 columns 49.3 / 46.6 / 45.2 / 41.9; 8K pairs of 7168 57.3 / 56.3 / 55.6 / 55.6; 16K of 7168
-//   109.0 / 108.3 / 105.9 / 105.9; 16K of 2048 35.5 / 36.0 / 37.1 / 41.8; 16K (top-1) of 1024 44.2 /
-//   41.3 / 42.9 / 50.5.
-constexpr int64_t kSmallMaxCounts = 1 << 24;
 // With fewer 4 KiB pieces than this the pieces are 1 KiB, so that every wave of the few groups has
 // one (128 tokens of 2048 columns, whole layer: 9.2 us against 10.8).
 constexpr int64_t kSmallWideUnits = 512;
-static int group_tokens(const Geom& g, int pieces) {
-  const int64_t most = std::min<int64_t>(kWave / g.k, (g.T + 255) / 256);
-  const int64_t want = pieces ? std::max<int64_t>(kLayoutWaves / pieces, (g.T * g.T * g.k + kSmallMaxCounts - 1) / kSmallMaxCounts)
-                              : most;
-  return (int)std::max<int64_t>(1, std::min(want, most));
-}
 
 // pieces: a row's 4 KiB chunks (fp8: passes) that the groups send, 0 for the layout alone.
 static SmallArgs small_args(const Geom& g, const int32_t* idx, const epl_layout_buffers& L, int pieces) {
@@ -306,7 +289,8 @@ hipError_t launch_small_layout_dispatch(const Geom& g, const int32_t* idx, const
                                         void* recv, float* recv_scale, int H, int pitch, int64_t cap, bool fp8,
                                         hipStream_t stream) {
   const int nv = H / 8;
-  const int pieces = fp8 ? (H + 1023) / 1024 : (nv + kBf16Cols - 1) / kBf16Cols;
+  static_assert(kBf16Cols * 8 == 2048, "small_pieces counts pieces of 2048 columns");
+  const int pieces = small_pieces(H, fp8);
   SmallArgs A = small_args(g, idx, L, pieces);
   A.x = static_cast<const u32x4*>(x);
   A.recv = static_cast<u32x4*>(recv);

@@ -27,8 +27,8 @@ def _launches(fn):
 
 
 @pytest.mark.parametrize("R,E,k,Tr,payload,launches", [
-    (4, 16, 2, 128, "bf16", 1), (16, 64, 8, 30, "fp8", 1), (1024, 1024, 2, 2, "bf16", 1),
-    (4, 64, 1, 4096, "bf16", 2), (2, 6, 1, 1500, "fp8", 2), (1024, 1024, 2, 3, "bf16", 2),
+    (4, 16, 2, 128, "bf16", 1), (16, 64, 8, 30, "fp8", 1), (1024, 1024, 2, 3, "bf16", 1),
+    (4, 64, 1, 4096, "bf16", 2), (2, 6, 1, 1500, "fp8", 2), (512, 1024, 2, 14, "bf16", 2),
     (64, 256, 8, 40, "bf16", 3), (16, 64, 8, 1024, "bf16", 3), (64, 256, 8, 40, "fp8", 3),
     (64, 512, 8, 64, "bf16", 4), (16, 512, 4, 300, "fp8", 4)])
 def test_reported_launches_are_issued(R, E, k, Tr, payload, launches):

@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("R,E,k,Tr,H,payload", [
     (32, 256, 8, 64, 512, "bf16"),      # 16384 pairs: the limit
     (4, 64, 1, 4096, 64, "bf16"),       # top-1, 4096 pairs per rank: groups of 64 tokens, rows in a second launch
-    (4, 64, 1, 704, 1032, "bf16"),      # the most tokens sent in one launch
+    (4, 64, 1, 1024, 1032, "bf16"),     # the most tokens sent in one launch
+    (1024, 1024, 1, 16, 72, "bf16"),    # 16384 tokens, in one launch: a group is a whole rank
+    (1024, 1024, 2, 8, 128, "fp8"),     # the same, fp8
     (1, 8, 1, 2816, 264, "bf16"),       # one rank and one choice: every lane adds to one word
     (1, 8, 2, 1201, 72, "bf16"),        # one rank, two choices
     (2, 6, 1, 1000, 512, "bf16"),       # two ranks of one choice

@@ -144,9 +144,11 @@ def test_place_kernel_chunks(geo):
 @pytest.mark.parametrize("R,E,k,Tr,H,fp8,one", [
     (16, 128, 8, 128, 2048, 0, 1), (32, 160, 8, 37, 5120, 0, 1), (4, 16, 2, 128, 256, 0, 1),  # decode shapes
     (16, 128, 8, 128, 2048, 1, 0), (16, 128, 8, 64, 7168, 1, 1), (8, 64, 4, 192, 2048, 1, 1), (8, 64, 4, 256, 4096, 1, 0),
-    (4, 64, 1, 704, 128, 0, 1), (4, 64, 1, 705, 128, 0, 0),    # 2816 and 2820 tokens
+    (4, 64, 2, 704, 128, 0, 1), (4, 64, 2, 705, 128, 0, 0),    # 2816 and 2820 tokens
+    (4, 64, 1, 1024, 128, 0, 1), (16, 64, 1, 257, 128, 0, 0), (2, 64, 1, 1409, 128, 0, 0),  # top-1: 4096 from four ranks on
     (4, 64, 1, 4096, 128, 0, 0), (64, 64, 2, 128, 128, 0, 0),  # where one launch took up to 1.47 times as long
-    (1, 8, 1, 4096, 2048, 1, 0), (8, 64, 5, 352, 128, 0, 0)])
+    (1024, 1024, 1, 16, 512, 0, 1), (1024, 1024, 1, 16, 512, 1, 1), (512, 512, 1, 32, 128, 0, 0),  # short ranks
+    (16, 64, 1, 128, 2048, 1, 1), (16, 64, 1, 129, 2048, 1, 0), (1, 8, 1, 4096, 2048, 1, 0), (8, 64, 5, 352, 128, 0, 0)])
 def test_small_layers_whose_rows_go_with_the_layout(geo, R, E, k, Tr, H, fp8, one):
     """The layers that take one launch, on both sides of each bound of the rule."""
     assert geo.small_dispatch(R, E, k, Tr, H, fp8) == one
