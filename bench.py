@@ -95,9 +95,7 @@ def algorithmic_bytes(T, k, H, R, E, P, payload):
     combine = P * H * 2 + 2 * T * k * 4 + T * H * 2
     placement = 4 * ((E + 1) + (R + 1) + E * R + 2 * T * k + 2 * P)  # offsets, pair rows/slots, recv_src/j
     layout = T * k * 4 + 4 * (R * E + R * R + T + 1) + placement
-    # The row kernel that follows the placement kernel also writes recv_src and recv_j.
-    return {"layout": layout, "dispatch": dispatch, "combine": combine, "rows_fused": dispatch + 4 * 2 * P,
-            "total": layout + dispatch + combine}
+    return {"layout": layout, "dispatch": dispatch, "combine": combine, "total": layout + dispatch + combine}
 
 
 LIB_PATH = os.path.join(ROOT, "paper_2607_06202_amd", "libepl.so")
@@ -786,20 +784,17 @@ def main():
     fabric_pairs = int(rc.sum() - np.trace(rc))
     row_bytes = w.H * 2 if w.payload == "bf16" else w.H + (w.H // 128) * 4
 
-    # The dispatch leg is one kernel: the plain dispatch kernel, the fused row kernel after the placement
-    # kernel, which also writes recv_src and recv_j, or the small layers' kernel, which does the layout too.
-    row_fused = mode == "fused" and launches == 3 and w.payload == "bf16"
+    # The dispatch leg is one kernel: the dispatch kernel, or the small layers', which does the layout too.
     if (mode == "decomposed" or one_kernel) and dom == "dispatch":
         dom_bytes = nbytes["layout"] + nbytes["dispatch"]  # the one launch does the whole layout and dispatch
     elif mode in layer_modes:
         dom, dom_bytes = "dispatch", nbytes["total"]  # the one launch is the whole layer
     else:
-        dom_bytes = nbytes["rows_fused" if row_fused and dom == "dispatch" else dom]
+        dom_bytes = nbytes[dom]
     achieved = dom_bytes / (dom_us * 1e-6) / 1e9
     kname = {"dispatch": "decomposed_kernel" if mode in ("decomposed",) + layer_modes else
              "dispatch_scheduled_kernel" if mode == "scheduled" else
              "route_single_kernel" if one_kernel else
-             "fused_bf16_kernel" if row_fused else
              "dispatch_fp8_kernel" if w.payload == "fp8" else "dispatch_bf16_kernel",
              "combine": "combine_kernel"}[dom]
     traffic = load_traffic(kname, w.name)

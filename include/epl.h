@@ -164,11 +164,9 @@ epl_status epl_layout_dispatch(const epl_config *cfg, const int32_t *topk_idx, c
  * apart (Kernel Decomposition: counts and prefix sums, then sending and reordering).
  * epl_layout_counts launches the layout kernels: one for small layouts (T*k <= 16384 and Tr*k <= 4096);
  * counts and placement for layouts of at most 512 chunks and 256 experts whose counts fit 16 bits (always up to
- * 480 chunks), whose bf16 row kernel writes recv_src and recv_j; otherwise histogram, scan and finalize. On
- * return (stream order) send_cnt, rank_cnt, tok_nranks and num_invalid are final; the other fields of L are
+ * 480 chunks); otherwise histogram, scan and finalize. On return (stream order) send_cnt, rank_cnt, tok_nranks and num_invalid are final; the other fields of L are
  * final only after epl_dispatch_rows. Statuses as epl_layout.
- * epl_dispatch_rows launches exactly one kernel: the row kernel that goes with it, or the
- * plain dispatch kernel. It must follow epl_layout_counts on the same stream (or be ordered
+ * epl_dispatch_rows launches exactly one kernel, that of epl_dispatch. It must follow epl_layout_counts on the same stream (or be ordered
  * after it) with the same cfg, topk_idx, L and workspace, none of them changed in between;
  * otherwise its outputs are undefined. Statuses as epl_layout_dispatch, all before the launch. */
 epl_status epl_layout_counts(const epl_config *cfg, const int32_t *topk_idx, const epl_layout_buffers *L,

@@ -90,24 +90,21 @@ epl_status check_layout_dispatch(const epl_config* cfg, const int32_t* topk_idx,
 bool is_fp8(const epl_config* cfg) { return cfg->payload == EPL_PAYLOAD_FP8_E4M3; }
 
 // The layout of epl_layout_dispatch where the rows are a launch of their own: one launch for small layouts,
-// two up to kPlaceMaxChunks chunks (recv_src and recv_j then belong to the bf16 row kernel), else three.
-hipError_t run_counts(const epl::Geom& g, const epl_config* cfg, const int32_t* topk_idx,
-                      const epl_layout_buffers* L, int32_t* ws, hipStream_t s) {
+// two up to kPlaceMaxChunks chunks, else three.
+hipError_t run_counts(const epl::Geom& g, const int32_t* topk_idx, const epl_layout_buffers* L, int32_t* ws,
+                      hipStream_t s) {
   if (epl::small_layout(g)) return epl::launch_small_layout(g, topk_idx, *L, s);
-  if (epl::place_layout(g)) return epl::launch_layout_place(g, topk_idx, ws, *L, is_fp8(cfg), s);
+  if (epl::place_layout(g)) return epl::launch_layout_place(g, topk_idx, ws, *L, s);
   return epl::launch_layout(g, topk_idx, ws, L->send_cnt, L->rank_cnt, L->expert_off, L->rank_off, L->seg_off,
                             L->tok_nranks, L->pair_row, L->pair_rslot, L->recv_src, L->recv_j, L->num_invalid, s);
 }
 
-// Its rows: the plain bf16 or fp8 dispatch kernel, or after the place kernel the fused one.
+// Its rows: the bf16 or fp8 dispatch kernel.
 hipError_t run_rows(const epl::Geom& g, const epl_config* cfg, const epl_layout_buffers* L, const void* x, void* recv,
                     float* recv_scale, int64_t cap, hipStream_t s) {
   if (is_fp8(cfg))
     return epl::launch_dispatch_fp8(x, L->pair_row, recv, recv_scale, g.T, cfg->topk, cfg->hidden, pitch_of(cfg),
                                     cap, s);
-  if (!epl::small_layout(g) && epl::place_layout(g))
-    return epl::launch_fused_dispatch(x, L->pair_row, recv, L->recv_src, L->recv_j, g.T, cfg->topk, cfg->hidden,
-                                      pitch_of(cfg), cap, s);
   return epl::launch_dispatch_bf16(x, L->pair_row, recv, g.T, cfg->topk, cfg->hidden, pitch_of(cfg), cap, s);
 }
 
@@ -118,7 +115,7 @@ hipError_t run_layout_dispatch(const epl::Geom& g, const epl_config* cfg, const 
   if (epl::small_dispatch(g, cfg->hidden, is_fp8(cfg)))
     return epl::launch_small_layout_dispatch(g, topk_idx, *L, x, recv, recv_scale, cfg->hidden, pitch_of(cfg), cap,
                                              is_fp8(cfg), s);
-  const hipError_t e = run_counts(g, cfg, topk_idx, L, ws, s);
+  const hipError_t e = run_counts(g, topk_idx, L, ws, s);
   return e != hipSuccess ? e : run_rows(g, cfg, L, x, recv, recv_scale, cap, s);
 }
 
@@ -158,7 +155,7 @@ EPL_EXPORT epl_status epl_layout_counts(const epl_config* cfg, const int32_t* to
                                         void* workspace, size_t ws_bytes, void* stream) {
   const epl_status st = check_layout_args(cfg, topk_idx, L, workspace, ws_bytes);
   if (st != EPL_OK) return st;
-  return from_hip(run_counts(make_geom(cfg), cfg, topk_idx, L, static_cast<int32_t*>(workspace),
+  return from_hip(run_counts(make_geom(cfg), topk_idx, L, static_cast<int32_t*>(workspace),
                              static_cast<hipStream_t>(stream)));
 }
 

@@ -36,49 +36,19 @@ namespace epl {
 // of 64K rows of 1024 138.7 / 143.3 / 136.3; top-2 of 32K rows of 7168 606 / 575 / 585, of 32K rows of
 // 512 55.1 / 57.2 / 55.5; top-4 of 16K rows of 4096 259 / 243 / 248.
 constexpr int plain_waves_per_simd(bool few) { return few ? 6 : 4; }
-template <class AtFn>
-__device__ __forceinline__ void plain_units(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row,
-                                            u32x4* __restrict__ recv, int64_t T, int k, int nv, int pv, int chunks,
-                                            int64_t cap, AtFn at) {
-  const int lane = threadIdx.x % kWave;
-  const int64_t units = T * chunks;
-  const int64_t stride = (int64_t)gridDim.x * kPlainWaves;
-  for (int64_t u = (int64_t)blockIdx.x * kPlainWaves + threadIdx.x / kWave; u < units; u += stride) {
-    const int64_t g = u / chunks;
-    const int c = (int)(u - g * chunks);
-    dispatch_bf16_unit(
-        x,
-        [&] {
-          const int row = lane < k ? pair_row[g * k + lane] : -1;
-          at(g, c, lane, row);
-          return row;
-        },
-        recv, g, c, k, nv, pv, cap, lane);
-  }
-}
-
 template <bool FEW>
 __global__ void __launch_bounds__(kPlainThreads)
     __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd(FEW), plain_waves_per_simd(FEW))))
     dispatch_bf16_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row, u32x4* __restrict__ recv,
                          int64_t T, int k, int nv, int pv, int chunks, int64_t cap) {
-  plain_units(x, pair_row, recv, T, k, nv, pv, chunks, cap, [](int64_t, int, int, int) {});
-}
-
-// The same after the place kernel, which leaves recv_src and recv_j to the wave that sends a token's
-// first columns: 4-byte stores to scattered rows, hidden among the row stores.
-template <bool FEW>
-__global__ void __launch_bounds__(kPlainThreads)
-    __attribute__((amdgpu_waves_per_eu(plain_waves_per_simd(FEW), plain_waves_per_simd(FEW))))
-    fused_bf16_kernel(const u32x4* __restrict__ x, const int32_t* __restrict__ pair_row, u32x4* __restrict__ recv,
-                      int32_t* __restrict__ recv_src, int32_t* __restrict__ recv_j, int64_t T, int k, int nv, int pv,
-                      int chunks, int64_t cap) {
-  plain_units(x, pair_row, recv, T, k, nv, pv, chunks, cap, [&](int64_t g, int c, int lane, int row) {
-    if (c == 0 && row >= 0 && row < T * k) {
-      recv_src[row] = (int32_t)g;
-      recv_j[row] = lane;
-    }
-  });
+  const int lane = threadIdx.x % kWave;
+  const int64_t units = T * chunks;
+  const int64_t stride = (int64_t)gridDim.x * kPlainWaves;
+  for (int64_t u = (int64_t)blockIdx.x * kPlainWaves + threadIdx.x / kWave; u < units; u += stride) {
+    const int64_t g = u / chunks;
+    dispatch_bf16_unit(x, [&] { return lane < k ? pair_row[g * k + lane] : -1; }, recv, g, (int)(u - g * chunks), k, nv,
+                       pv, cap, lane);
+  }
 }
 
 // The fp8 kernel is capped at kFp8WavesPerSimd waves per SIMD. The compiler enforces the cap by
@@ -122,25 +92,6 @@ hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* re
   else
     hipLaunchKernelGGL(dispatch_bf16_kernel<false>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, T, k, nv,
                        pitch / 8, chunks, cap);
-  return hipGetLastError();
-}
-
-hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* recv, int32_t* recv_src,
-                                 int32_t* recv_j, int64_t T, int k, int H, int pitch, int64_t cap,
-                                 hipStream_t stream) {
-  if (T == 0) return hipSuccess;
-  const int nv = H / 8;
-  const int chunks = (nv + kWave - 1) / kWave;
-  const int64_t units = T * chunks;
-  const dim3 grid(unit_grid(units, kPlainWaves, kPlainThreads));
-  const u32x4* xv = static_cast<const u32x4*>(x);
-  u32x4* rv = static_cast<u32x4*>(recv);
-  if (k <= kFewChoices)
-    hipLaunchKernelGGL(fused_bf16_kernel<true>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, recv_src,
-                       recv_j, T, k, nv, pitch / 8, chunks, cap);
-  else
-    hipLaunchKernelGGL(fused_bf16_kernel<false>, grid, dim3(kPlainThreads), 0, stream, xv, pair_row, rv, recv_src,
-                       recv_j, T, k, nv, pitch / 8, chunks, cap);
   return hipGetLastError();
 }
 

@@ -233,10 +233,9 @@ hipError_t launch_layout_counts(const Geom& g, const int32_t* idx, int32_t* ws, 
 hipError_t launch_layout_finalize(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* expert_off,
                                   int32_t* rank_off, int32_t* seg_off, int32_t* pair_row, int32_t* pair_rslot,
                                   int32_t* recv_src, int32_t* recv_j, hipStream_t stream);
-// The geometries place_layout accepts: the whole layout in two launches (count and place), recv_src and
-// recv_j only with write_src.
+// The geometries place_layout accepts: the whole layout in two launches (count and place).
 hipError_t launch_layout_place(const Geom& g, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
-                               bool write_src, hipStream_t stream);
+                               hipStream_t stream);
 hipError_t launch_layout(const Geom& g, const int32_t* idx, int32_t* ws, int32_t* send_cnt, int32_t* rank_cnt,
                          int32_t* expert_off, int32_t* rank_off, int32_t* seg_off, int32_t* tok_nranks,
                          int32_t* pair_row, int32_t* pair_rslot, int32_t* recv_src, int32_t* recv_j,
@@ -254,10 +253,6 @@ hipError_t launch_dispatch_bf16(const void* x, const int32_t* pair_row, void* re
                                 int pitch, int64_t cap, hipStream_t stream);
 hipError_t launch_dispatch_fp8(const void* x, const int32_t* pair_row, void* recv, float* recv_scale, int64_t T,
                                int k, int H, int pitch, int64_t cap, hipStream_t stream);
-// The bf16 dispatch after launch_layout_place without write_src: it also writes recv_src and recv_j.
-hipError_t launch_fused_dispatch(const void* x, const int32_t* pair_row, void* recv, int32_t* recv_src,
-                                 int32_t* recv_j, int64_t T, int k, int H, int pitch, int64_t cap,
-                                 hipStream_t stream);
 // The geometries whose tokens the decomposed launch can place one by one.
 bool token_rows_ok(const Geom& g);
 // The decomposed single-launch layout and dispatch (bf16, the geometries token_rows_ok

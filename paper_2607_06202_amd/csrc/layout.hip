@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(kLayoutThreads)
   for (int i = tid; i < kLayoutWaves * (G.E + G.R); i += kLayoutThreads) whe[i] = 0;
 
   const int32_t* src = idx + g0 * G.k;
-  assign_chunk_rows<kLayoutWaves, kChunkSteps, kLayoutThreads, true, false>(
+  assign_chunk_rows<kLayoutWaves, kChunkSteps, kLayoutThreads, false>(
       G, nt, g0, [&](int, int t, bool in) { return in ? src[t * G.k + lane_id()] : -1; },
       [&] {
 #pragma unroll
@@ -218,8 +218,11 @@ __global__ void __launch_bounds__(kCountThreads)
 // LDS word of expert e's count, so that the lanes of a wave, eight experts apart, hit consecutive words.
 __device__ __forceinline__ int place_slot(int e) { return (e & 7) * kPlaceLanes + (e >> 3); }
 
-// STEPS bounds the four waves' steps through the chunk. SRC also writes recv_src and recv_j.
-template <int STEPS, bool SRC>
+// STEPS bounds the four waves' steps through the chunk. It writes recv_src and recv_j as well, 4 bytes to
+// scattered rows; left to the row kernel's waves, among their row stores, they delayed those (layout, dispatch and
+// combine, us here / there: 64 ranks x 128 tokens x 2048 columns 112.1 / 115.5, x 7168 373.9 / 375.7; 32 x 4096 top-1 x
+// 128 100.3 / 102.6; 32 x 128 x 4096 111.6 / 115.2).
+template <int STEPS>
 __global__ void __launch_bounds__(kLayoutThreads)
     route_place_kernel(Geom G, const int32_t* __restrict__ idx, const int32_t* __restrict__ cnt,
                        const int32_t* __restrict__ group_cnt, const int32_t* __restrict__ chunk_r,
@@ -274,7 +277,7 @@ __global__ void __launch_bounds__(kLayoutThreads)
   if (to_rank || to_chunk) __builtin_memcpy(&sv, cnt + (int64_t)single * words + word0, 16);
   clear_lds<kLayoutThreads>(lds, kParts * kPlaceExperts + 2 * G.R + kLayoutWaves * (G.E + G.R));
   int total = 0;
-  assign_chunk_rows<kLayoutWaves, STEPS, kLayoutThreads, SRC, true>(
+  assign_chunk_rows<kLayoutWaves, STEPS, kLayoutThreads, true>(
       G, nt, g0, [&](int, int t, bool in) { return in ? src[t * G.k + lane_id()] : -1; },
       [&] {  // the ranks were worked out while the counts were in flight
         u16x2 part[3][4] = {};
@@ -353,7 +356,7 @@ static size_t finalize_lds_bytes(const Geom& g) {
 }
 
 hipError_t launch_layout_place(const Geom& geom, const int32_t* idx, int32_t* ws, const epl_layout_buffers& L,
-                               bool write_src, hipStream_t stream) {
+                               hipStream_t stream) {
   if (!place_layout(geom)) return hipErrorInvalidValue;  // its callers ask first
   const WsLayout wl = ws_layout(geom);
   const Geom g = place_geom(geom);
@@ -369,16 +372,10 @@ hipError_t launch_layout_place(const Geom& geom, const int32_t* idx, int32_t* ws
   const size_t lds = sizeof(int32_t) * ((size_t)5 * kPlaceExperts + 2 * g.R + (size_t)kLayoutWaves * (g.E + g.R) +
                                         2 * g.E + 1);
   const dim3 grid(g.nblk), block(kLayoutThreads);
-  if (few && write_src)
-    hipLaunchKernelGGL((route_place_kernel<2, true>), grid, block, lds, stream, g, idx, cnt, group_cnt, chunk_r, L);
-  else if (few)
-    hipLaunchKernelGGL((route_place_kernel<2, false>), grid, block, lds, stream, g, idx, cnt, group_cnt, chunk_r, L);
-  else if (write_src)
-    hipLaunchKernelGGL((route_place_kernel<kChunkSteps, true>), grid, block, lds, stream, g, idx, cnt, group_cnt,
-                       chunk_r, L);
+  if (few)
+    hipLaunchKernelGGL(route_place_kernel<2>, grid, block, lds, stream, g, idx, cnt, group_cnt, chunk_r, L);
   else
-    hipLaunchKernelGGL((route_place_kernel<kChunkSteps, false>), grid, block, lds, stream, g, idx, cnt, group_cnt,
-                       chunk_r, L);
+    hipLaunchKernelGGL(route_place_kernel<kChunkSteps>, grid, block, lds, stream, g, idx, cnt, group_cnt, chunk_r, L);
   return hipGetLastError();
 }
 

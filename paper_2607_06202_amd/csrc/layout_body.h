@@ -131,11 +131,11 @@ __device__ __forceinline__ void hist_chunk(const Geom& G, int b, const int32_t* 
 // * whe/whr [WAVES][E] and [WAVES][R]: zeroed.
 // Every pair gets its stable rank among equal keys of the chunk: one ballot per key bit, popcount of
 // the lanes below, and per-wave LDS running counts; a cross-wave prefix then yields pair_row,
-// pair_rslot and (with SRC) recv_src and recv_j. P is the number of valid pairs in the whole layout;
+// pair_rslot, recv_src and recv_j. P is the number of valid pairs in the whole layout;
 // rows at or past it are never written. load(q, t, in) returns the lane's id in the wave's step q, whose
 // first token is t; it runs before anything waits. ready() runs between the ranks and their use: base_e, base_r
 // and P must be there after it, and it synchronises the workgroup. NRANKS also writes tok_nranks.
-template <int WAVES, int STEPS, int THREADS, bool SRC, bool NRANKS, class LoadFn, class ReadyFn>
+template <int WAVES, int STEPS, int THREADS, bool NRANKS, class LoadFn, class ReadyFn>
 __device__ __forceinline__ void assign_chunk_rows(const Geom& G, int nt, int64_t g0, LoadFn load, ReadyFn ready,
                                                   const int32_t* base_e, const int32_t* base_r, int32_t* whe,
                                                   int32_t* whr, int32_t* __restrict__ pair_row,
@@ -224,11 +224,9 @@ __device__ __forceinline__ void assign_chunk_rows(const Geom& G, int nt, int64_t
       const int64_t p = (g0 + t) * G.k + lane;
       pair_row[p] = row;
       pair_rslot[p] = valid ? rslot : -1;
-      if constexpr (SRC) {
-        if (valid && row < total) {  // always true for a consistent layout; keeps stores in bounds
-          recv_src[row] = (int32_t)(g0 + t + P.tl);
-          recv_j[row] = P.j;
-        }
+      if (valid && row < total) {  // always true for a consistent layout; keeps stores in bounds
+        recv_src[row] = (int32_t)(g0 + t + P.tl);
+        recv_j[row] = P.j;
       }
     }
   }

@@ -30,15 +30,14 @@ def test_decode_bytes_from_the_sizes_of_x_and_recv():
     assert abs(b["total"] / (0.7 * 8e12) * 1e6 - 377.9) < 0.05
 
 
-def test_fused_row_kernel_bytes_add_what_it_writes_of_the_layout():
-    """The row kernel that follows the placement kernel writes recv_src and recv_j on top of the dispatch's
-    own bytes; the expert, rank and segment offsets and the pair rows and slots are the placement kernel's."""
+def test_layout_bytes_hold_the_placement_metadata():
+    """The layout reads the ids and writes the counts, the expert, rank and segment offsets, the pair rows and
+    slots, and recv_src / recv_j; the row kernel writes none of them."""
     b = _bytes("decode_ep64")
     R, E, T, k, P = 64, 256, 8192, 8, 65536
     placement = 4 * ((E + 1) + (R + 1) + E * R + 2 * T * k + 2 * P)
     assert placement == 1_115_400
-    assert b["rows_fused"] == b["dispatch"] + 2 * P * 4
-    assert placement < b["layout"]  # the layout accounts for all of them once in the total
+    assert b["layout"] == 4 * T * k + 4 * (R * E + R * R + T + 1) + placement
 
 
 def test_per_rank_payload_matches_the_papers_bandwidth_table():
@@ -123,7 +122,7 @@ def test_code_hashes_of_the_built_library():
         pytest.skip("libepl.so is not built")
     h = bench.kernel_code_hashes()
     assert {"route_hist_kernel", "route_scan_kernel", "route_finalize_kernel", "route_single_kernel",
-            "dispatch_bf16_kernel", "dispatch_fp8_kernel", "fused_bf16_kernel", "combine_kernel",
+            "route_count_kernel", "route_place_kernel", "dispatch_bf16_kernel", "dispatch_fp8_kernel", "combine_kernel",
             "locate_rows_kernel"} <= set(h)
 
 

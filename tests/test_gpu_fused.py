@@ -1,7 +1,7 @@
 """epl_layout_dispatch, and its two phases epl_layout_counts + epl_dispatch_rows, against the CPU
 oracle: every layout output and the bf16 / fp8 payload, bit for bit. Every case asserts how many launches
 the call takes:
-* 3, counts and placement and then the rows, of which the bf16 kernel also writes recv_src and recv_j:
+* 3, counts and placement and then the rows:
   ragged last chunks, duplicates, invalid ids, 1 and 2 experts per rank, more choices than experts, rows of
   one to twenty 1 KiB chunks, ragged ones, so that a workgroup's two waves take one token or two;
 * 4, the three-launch layout then the dispatch (more experts or chunks);
@@ -145,8 +145,7 @@ def test_layout_dispatch_random_shapes(seed):
 
 
 def test_row_kernel_after_placement_with_long_rows():
-    """Rows of 32 1 KiB chunks after the placement kernel (64 ranks of 100 tokens at H = 16,384), of which only a
-    token's first writes recv_src and recv_j. The layout against the oracle; every packed row against its
+    """Rows of 32 1 KiB chunks after the placement kernel (64 ranks of 100 tokens at H = 16,384). The layout against the oracle; every packed row against its
     source row, bit for bit."""
     dev = device()
     R, E, k, Tr, H = 64, 256, 8, 100, 16384
