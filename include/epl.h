@@ -228,9 +228,10 @@ int epl_decomposed_plan(const epl_config *cfg, int32_t count_groups, int32_t *gr
  * dispatched rows (the combine reads recv itself), the combine synchronised with the dispatch per
  * row by Sentinel Polling (Data-as-Flag; Sentinel Polling variant) instead of a kernel boundary.
  * Count and send workgroups work as in epl_layout_dispatch_decomposed; then every workgroup
- * combines: it works out each token's rows, loads each 16-byte piece of a row with device-scope
- * loads until none of its elements is EPL_SENTINEL_BF16, folds it (the arithmetic of epl_combine,
- * bit for bit), and writes the sentinel back over it (the reset after consumption).
+ * combines (for few tokens, and for many short rows, workgroups of their own do): it works out each
+ * token's rows, loads each 16-byte piece of a row with device-scope loads until none of its elements
+ * is EPL_SENTINEL_BF16, folds it (the arithmetic of epl_combine, bit for bit), and writes the
+ * sentinel back over it (the reset after consumption).
  *   recv       recv_rows_cap rows of pitch bf16 elements: elements 0..H-1 of every row must hold
  *              EPL_SENTINEL_BF16 before the first call (epl_sentinel_fill over the whole buffer);
  *              each call leaves them so. No other call may write them in between.
